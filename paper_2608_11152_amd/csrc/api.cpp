@@ -323,6 +323,7 @@ struct DecodeLayout {
   kvp::DecodePlan plan;
   std::vector<int32_t> merge_info;  // one 16-byte record per merged sequence: {seq, first partial, count, 0}
   size_t off_wave = 0, off_seg = 0, off_group = 0, off_members = 0, off_part_base = 0, off_merge = 0;
+  int max_parts = 0;                // largest partial count of a merged sequence
   size_t meta_bytes = 0;            // work list bytes (offsets above, 256-byte aligned)
   size_t off_acc = 0, off_ml = 0, total = 0;
 
@@ -353,6 +354,7 @@ int layout_decode(kvp_pool_t pool, const int32_t* seq_lens, int B, int maxp, con
     L->merge_info[4 * k] = seq;
     L->merge_info[4 * k + 1] = P.part_base[seq];
     L->merge_info[4 * k + 2] = P.n_parts[seq];
+    L->max_parts = std::max(L->max_parts, P.n_parts[seq]);
     L->merge_info[4 * k + 3] = 0;
   }
   size_t at = 0;
@@ -411,12 +413,13 @@ kvp::DecodeArgs decode_args(const DecodeLayout& L, kvp_pool_t pool, int layer, c
 
 // The merge of split partials (decode: one record per split sequence; prefill: one per query row of a
 // split session), enqueued after the kernels that write the partials.
-hipError_t launch_merge(const int32_t* merge_info, int n_merge, const float* part_acc, const float2* part_ml,
+hipError_t launch_merge(const int32_t* merge_info, int n_merge, int max_parts, const float* part_acc, const float2* part_ml,
                         void* out, int out_f32, int num_q_heads, kvp_pool_t pool, hipStream_t s) {
   if (n_merge == 0) return hipSuccess;
   kvp::MergeArgs mg{};
   mg.merge_info = merge_info;
   mg.n_merge = n_merge;
+  mg.max_parts = max_parts;
   mg.part_acc = part_acc;
   mg.part_ml = part_ml;
   mg.out = out;
@@ -436,7 +439,7 @@ hipError_t launch_decode_plan(const DecodeLayout& L, kvp_pool_t pool, int layer,
   hipError_t e = kvp::launch_decode(a, pool->head_dim, s);
   if (e == hipSuccess)
     e = launch_merge(reinterpret_cast<const int32_t*>(meta + L.off_merge), (int)L.plan.merge_seqs.size(),
-                     a.part_acc, a.part_ml, out, a.out_f32, num_q_heads, pool, s);
+                     L.max_parts, a.part_acc, a.part_ml, out, a.out_f32, num_q_heads, pool, s);
   return e;
 }
 
@@ -459,6 +462,7 @@ struct PrefillLayout {
   kvp::PrefillPlan plan;
   Packer meta;
   size_t off_items = 0, off_ctx = 0, off_cuq = 0, off_part_base = 0, off_nsplit = 0, off_merge = 0;
+  int max_parts = 0;  // largest range count of a merged query row
   size_t off_acc = 0, off_ml = 0, total = 0;
 };
 
@@ -467,6 +471,7 @@ int layout_prefill(kvp_pool_t pool, const int32_t* ctx_lens, const int32_t* cu_q
   kvp::Status st = kvp::plan_prefill(ctx_lens, cu_q, B, maxp, Hq, pool->num_kv_heads, &L->plan);
   if (!st.ok()) return from_status(st);
   const auto& P = L->plan;
+  for (int32_t n : P.nsplit) L->max_parts = std::max(L->max_parts, n);
   L->off_items = L->meta.add(P.items.data(), P.items.size() * sizeof(kvp::PrefillItem));
   L->off_ctx = L->meta.add(ctx_lens, (size_t)B * 4);
   L->off_cuq = L->meta.add(cu_q, (size_t)(B + 1) * 4);
@@ -1155,7 +1160,7 @@ int prefix_chunk_prefill_attn(const void* q, kvp_pool_t pool, int layer, const i
   // split tiles: combine each query row's key ranges (the decode merge, one record per query row)
   if (e == hipSuccess)
     e = launch_merge(reinterpret_cast<const int32_t*>(w + L.off_merge), (int)(L.plan.merge_info.size() / 4),
-                     a.part_acc, a.part_ml, out, a.out_f32, num_q_heads, pool, s);
+                     L.max_parts, a.part_acc, a.part_ml, out, a.out_f32, num_q_heads, pool, s);
   return e == hipSuccess ? KVP_OK : hip_err(e, "prefix_chunk_prefill_attn launch");
 }
 
@@ -1229,11 +1234,11 @@ int mixed_step_attn(kvp_pool_t pool, int layer, int num_q_heads, float scale, in
   if (e == hipSuccess && num_dec > 0)
     e = launch_merge(reinterpret_cast<const int32_t*>(reinterpret_cast<const unsigned char*>(lease.host) +
                                                       L.dec.off_merge),
-                     (int)L.dec.plan.merge_seqs.size(), d.part_acc, d.part_ml, out_dec, d.out_f32, num_q_heads,
+                     (int)L.dec.plan.merge_seqs.size(), L.dec.max_parts, d.part_acc, d.part_ml, out_dec, d.out_f32, num_q_heads,
                      pool, s);
   if (e == hipSuccess && has_pf)
     e = launch_merge(reinterpret_cast<const int32_t*>(w + L.off_pf + L.pf.off_merge),
-                     (int)(L.pf.plan.merge_info.size() / 4), p.part_acc, p.part_ml, out_pf, p.out_f32, num_q_heads,
+                     (int)(L.pf.plan.merge_info.size() / 4), L.pf.max_parts, p.part_acc, p.part_ml, out_pf, p.out_f32, num_q_heads,
                      pool, s);
   const int rr = num_dec > 0 ? staging().release(lease, s, e == hipSuccess) : KVP_OK;
   if (e != hipSuccess) return hip_err(e, "mixed_step_attn launch");

@@ -55,20 +55,26 @@ __global__ __launch_bounds__(256) void decode_kernel(DecodeArgs a) {
 // Log-sum-exp merge: out = sum_j acc_j 2^(m_j - m) / sum_j l_j 2^(m_j - m), m = max_j m_j, in a fixed
 // order (so results are deterministic).  Empty partials (m = -inf, l = 0) carry zero weight; a
 // sequence with no partial gets a zero output.  One workgroup per (sequence, KV head, group of hw query
-// heads), started from one 16-byte record {seq, first partial, partial count}; hw is chosen per call so
-// that few sequences still spread over enough workgroups and many do not pay for extra ones.
-// T = 256 / (hw * D / 4) consecutive lanes share each output float4: lane q loads partials q, q + T, ...
-// (accumulator and (m, l) together, all in flight at once), folds them with a running max, and the T
-// lanes are then combined by shuffles, so the whole merge costs one round of memory latency.
+// heads, 1 / dsplit of the head dim), started from one 16-byte record {seq, first partial, partial count};
+// hw and dsplit are chosen per call so that few sequences still spread over enough workgroups and many do
+// not pay for extra ones.  T = 256 / (hw * D / 4 / dsplit) consecutive lanes share each output float4:
+// lane q loads partials q, q + T, ... (accumulator and (m, l) together, 16 in flight at once), folds them
+// with a running max, and the T lanes are then combined by shuffles.
+// Bound: latency of the rounds of 16 loads.  One sequence of 131,007 tokens has 512 partials: whole head
+// rows (T = 8, 4 rounds, 32 workgroups) took 19.1 us and the call 72.1 us, quarter rows (T = 32, 1 round, 128
+// workgroups) take the call to 61.2 us.
 // ---------------------------------------------------------------------------------------------------
+constexpr int kMergeInFlight = 16;  // partials in flight per lane
+
 template <int D>
 __global__ __launch_bounds__(256) void decode_merge_kernel(MergeArgs a) {
-  constexpr int V4 = D / 4;  // float4 per head row
-  constexpr int U = 16;      // partials in flight per lane
+  constexpr int U = kMergeInFlight;
+  const int V4 = D / 4 / a.dsplit;  // float4 per head row of this workgroup
   const int G = a.Hq / a.Hkv;
   const int hw = a.hw;
   const int nsplit = G / hw;
-  const int b = blockIdx.x;
+  const int dsub = blockIdx.x % a.dsplit;
+  const int b = blockIdx.x / a.dsplit;
   const int rest = b / nsplit;
   const int sub = b - rest * nsplit;
   const int grp = rest / a.Hkv;
@@ -77,9 +83,9 @@ __global__ __launch_bounds__(256) void decode_merge_kernel(MergeArgs a) {
   const int seq = info.x, P = info.z;
   const int64_t base = info.y;
   const int tid = threadIdx.x;
-  const int T = 256 / (hw * V4);  // lanes per output float4: 1 to 16 (a divisor of 64)
+  const int T = 256 / (hw * V4);  // lanes per output float4: 1 to 64 (a divisor of 64)
   const int e = tid / T, q = tid - e * T;
-  const int hh = e / V4, d4 = e - hh * V4;
+  const int hh = e / V4, d4 = dsub * V4 + e - hh * V4;
   const int h = kvh * G + sub * hw + hh;
   const int64_t sa = (int64_t)a.Hq * D;
   const float* pa = a.part_acc + (base * a.Hq + h) * D + 4 * d4;
@@ -203,14 +209,20 @@ hipError_t launch_decode(const DecodeArgs& a, int D, hipStream_t s) {
 hipError_t launch_decode_merge(const MergeArgs& a, int D, hipStream_t s) {
   if (a.n_merge == 0) return hipSuccess;
   // Split the query heads of a (sequence, KV head) over up to G workgroups while the grid stays at or
-  // under 1024 workgroups; at most 256 threads' worth of float4 outputs per workgroup.
+  // under 1024 workgroups; at most 256 threads' worth of float4 outputs per workgroup.  Then split the head
+  // dim by up to 4 within the same bound while a lane would take more than one round of partials; past one
+  // round there is nothing to gain (tiny calls of 2 partials: 3.8 us either way).
   const int G = a.Hq / a.Hkv;
   const int64_t units = (int64_t)a.n_merge * a.Hkv;
   int nsplit = 1;
   while (2 * nsplit <= G && (units * 2 * nsplit <= 1024 || G / nsplit > 1024 / D)) nsplit *= 2;
   MergeArgs m = a;
   m.hw = G / nsplit;
-  const dim3 grid((unsigned)(units * nsplit));
+  m.dsplit = 1;
+  while (m.dsplit < 4 && m.hw == 1 && units * nsplit * m.dsplit * 2 <= 1024 &&
+         a.max_parts > kMergeInFlight * (1024 / D) * m.dsplit)
+    m.dsplit *= 2;
+  const dim3 grid((unsigned)(units * nsplit * m.dsplit));
   if (D == 128) hipLaunchKernelGGL(decode_merge_kernel<128>, grid, dim3(256), 0, s, m);
   else hipLaunchKernelGGL(decode_merge_kernel<64>, grid, dim3(256), 0, s, m);
   return hipGetLastError();
