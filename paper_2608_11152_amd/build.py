@@ -20,11 +20,16 @@ BUILD_DIR = os.path.join(ROOT, "_build")
 LIB_NAME = "libkvpattn.so"
 LIB_PATH = os.path.join(HERE, LIB_NAME)
 
-SOURCES = ["plan.cpp", "api.cpp", "append.hip", "decode.hip", "prefill.hip", "mixed.hip", "tier.hip", "prefix.hip"]
+SOURCES = ["plan.cpp", "api.cpp", "append.hip", "decode.hip", "prefill.hip", "prefill_long.hip", "tier.hip", "prefix.hip"]
 ARCH = "gfx950"
 COMMON = ["-O3", "-fPIC", "-std=c++17", "-Wall", "-Wno-unused-result", f"-I{os.path.join(ROOT, 'include')}"]
 HIP_ONLY = [f"--offload-arch={ARCH}", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
             "-munsafe-fp-atomics"]
+
+
+# prefill_long.hip: matrix results in architectural registers (the softmax reads the scores there without copies;
+# the compiler's own choice for a 512-register kernel is the accumulation registers).
+EXTRA = {"prefill_long.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]}
 
 
 def _hipcc() -> str:
@@ -37,7 +42,7 @@ def _hipcc() -> str:
 def _compile(src: str, hipcc: str) -> str:
     obj = os.path.join(BUILD_DIR, os.path.splitext(src)[0] + ".o")
     path = os.path.join(CSRC, src)
-    cmd = [hipcc, "-x", "hip", *HIP_ONLY, *COMMON, "-c", path, "-o", obj]
+    cmd = [hipcc, "-x", "hip", *HIP_ONLY, *COMMON, *EXTRA.get(src, []), "-c", path, "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)
     noise = "is not a recognized feature for this target"
     err = "\n".join(l for l in (r.stderr or "").splitlines() if noise not in l)

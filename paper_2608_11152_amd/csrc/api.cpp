@@ -29,8 +29,11 @@ struct kvp_pool {
   std::vector<float> k_scale, v_scale;  // per layer, FP8 pools
   size_t layer_bytes = 0;
   unsigned char* base = nullptr;  // [layers][pages][Hkv][2][16*d] bf16
-  int* err = nullptr;             // device error word
+  int* err = nullptr;             // device error word, then a block of zeros (kErrBytes)
 };
+
+// The error word's line, then zeros as large as the largest (page, head) block (bf16, d = 128).
+constexpr size_t kErrLine = 256, kErrBytes = kErrLine + 2 * 2 * 16 * 128;
 
 // Scratch of the allocation-free decode entry point: the work list and the split-KV partials of one
 // call, in device memory the code object brings (every GPU the library runs on holds its own copy until
@@ -70,8 +73,7 @@ int hip_err(hipError_t e, const char* what) {
 // Pieces are cut from blocks, each open for one stream; a block that has no room for the next piece is closed
 // by recording one event behind its work, and is used again once the event has completed.  An event behind
 // every call costs the stream a 5.6 us gap before its next kernel (kernel trace; no gap between kernels
-// without one), more than the host's share of it: mixed decode 371 -> 365 us, RLHF 180 -> 174 us, a 67 MB
-// append 20.8 -> 16.4 us.  Blocks open for a stream that has gone quiet are not reused (nothing was recorded
+// without one): mixed decode 371.8 -> 369.1 us, RLHF 180.2 -> 177.2 us, a 67 MB append 20.7 -> 17.2 us without.  Blocks open for a stream that has gone quiet are not reused (nothing was recorded
 // behind their work), so at most kMaxOpen of them stay open: past that every release closes its block.
 class Staging {
  public:
@@ -543,7 +545,7 @@ int check_decode_args(kvp_pool_t pool, int layer, const void* q, const int32_t* 
 struct PrefillLayout {
   kvp::PrefillPlan plan;
   Packer meta;
-  size_t off_items = 0, off_ctx = 0, off_cuq = 0, off_part_base = 0, off_nsplit = 0, off_merge = 0;
+  size_t off_items = 0, off_merge = 0;
   int max_parts = 0;  // largest range count of a merged query row
   size_t off_acc = 0, off_ml = 0, total = 0;
 };
@@ -554,11 +556,8 @@ int layout_prefill(kvp_pool_t pool, const int32_t* ctx_lens, const int32_t* cu_q
   if (!st.ok()) return from_status(st);
   const auto& P = L->plan;
   for (int32_t n : P.nsplit) L->max_parts = std::max(L->max_parts, n);
-  L->off_items = L->meta.add(P.items.data(), P.items.size() * sizeof(kvp::PrefillItem));
-  L->off_ctx = L->meta.add(ctx_lens, (size_t)B * 4);
-  L->off_cuq = L->meta.add(cu_q, (size_t)(B + 1) * 4);
-  L->off_part_base = L->meta.add(P.part_base.data(), P.part_base.size() * 4);
-  L->off_nsplit = L->meta.add(P.nsplit.data(), P.nsplit.size() * 4);
+  const std::vector<kvp::PrefillWork> work = kvp::prefill_work(P, ctx_lens, cu_q, Hq / pool->num_kv_heads);
+  L->off_items = L->meta.add(work.data(), work.size() * sizeof(kvp::PrefillWork));
   L->off_merge = L->meta.add(P.merge_info.data(), P.merge_info.size() * 4);
   L->off_acc = L->meta.size();
   L->off_ml = L->off_acc + (((size_t)P.total_parts * Hq * pool->head_dim * 4 + 255) & ~size_t(255));
@@ -576,12 +575,10 @@ kvp::PrefillArgs prefill_args(const PrefillLayout& L, kvp_pool_t pool, int layer
   a.layer = layer_ptr(pool, layer);
   a.bt = block_tables;
   a.maxp = maxp;
-  a.items = reinterpret_cast<const kvp::PrefillItem*>(w + L.off_items);
+  a.items = reinterpret_cast<const kvp::PrefillWork*>(w + L.off_items);
   a.n_items = (int)L.plan.items.size();
-  a.ctx_lens = reinterpret_cast<const int32_t*>(w + L.off_ctx);
-  a.cu_q = reinterpret_cast<const int32_t*>(w + L.off_cuq);
-  a.part_base = reinterpret_cast<const int32_t*>(w + L.off_part_base);
-  a.nsplit = reinterpret_cast<const int32_t*>(w + L.off_nsplit);
+  a.long_items = pool->dtype == KVP_BF16 && pool->head_dim == 128 && kvp::prefill_items_long(L.plan);
+  a.zero = reinterpret_cast<const unsigned char*>(pool->err) + kErrLine;
   a.part_acc = reinterpret_cast<float*>(w + L.off_acc);
   a.part_ml = reinterpret_cast<float2*>(w + L.off_ml);
   a.out = out;
@@ -683,9 +680,9 @@ int kv_pool_create(kvp_pool_t* out, int num_layers, int num_pages, int page_size
     delete p;
     return set_err(KVP_ENOMEM, "hipMalloc(pool of %zu bytes): %s", want, hipGetErrorString(e));
   }
-  e = hipMalloc(reinterpret_cast<void**>(&p->err), 256);
+  e = hipMalloc(reinterpret_cast<void**>(&p->err), kErrBytes);
   if (e == hipSuccess) e = kvp::launch_fill_zero(p->base, p->layer_bytes * num_layers, nullptr);
-  if (e == hipSuccess) e = kvp::launch_fill_zero(p->err, 256, nullptr);
+  if (e == hipSuccess) e = kvp::launch_fill_zero(p->err, kErrBytes, nullptr);
   if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
   if (e != hipSuccess) {
     (void)hipFree(p->base);
@@ -1297,22 +1294,8 @@ int mixed_step_attn(kvp_pool_t pool, int layer, int num_q_heads, float scale, in
     p = prefill_args(L.pf, pool, layer, q_pf, block_tables_pf, maxp_pf, num_q_heads, scale, out_pf, out_dtype,
                      w + L.off_pf);
   }
-  if (num_dec > 0 && !has_pf) {
-    e = kvp::launch_decode(d, pool->head_dim, s);                   // the decode call's own launch
-  } else if (num_dec == 0) {
-    e = kvp::launch_prefill(p, pool->head_dim, s);                  // the prefill call's own launch
-  } else {
-    // LDS-staged shared-prefix blocks (wide groups over long prompts) run in a launch of their own ahead
-    // of the fused one, which carries the wave-path blocks and the prefill blocks.
-    if (d.n_group_blocks > 0) {
-      kvp::DecodeArgs g = d;
-      g.n_wave_blocks = 0;
-      e = kvp::launch_decode(g, pool->head_dim, s);
-    }
-    kvp::DecodeArgs wv = d;
-    wv.n_group_blocks = 0;
-    if (e == hipSuccess) e = kvp::launch_mixed_step(wv, p, pool->head_dim, pool->dtype == KVP_FP8_E4M3, s);
-  }
+  if (num_dec > 0) e = kvp::launch_decode(d, pool->head_dim, s);
+  if (e == hipSuccess && has_pf) e = kvp::launch_prefill(p, pool->head_dim, s);
   if (e == hipSuccess && num_dec > 0)
     e = launch_merge(reinterpret_cast<const int32_t*>(reinterpret_cast<const unsigned char*>(lease.host) +
                                                       L.dec.off_merge),

@@ -87,12 +87,10 @@ struct PrefillArgs {
   const uint16_t* layer;
   const int32_t* bt;
   int maxp;
-  const PrefillItem* items;
+  const PrefillWork* items;
   int n_items;
-  const int32_t* ctx_lens;  // device copies
-  const int32_t* cu_q;
-  const int32_t* part_base; // [B] first partial of each session (split sessions only)
-  const int32_t* nsplit;    // [B] key ranges per query row
+  bool long_items;          // the kernel for long key ranges (prefill_items_long)
+  const unsigned char* zero;  // one (page, head) block of zeros, read in the place of a page outside the pool
   float* part_acc;          // [parts, Hq, D] unnormalised accumulators of split tiles
   float2* part_ml;          // [parts, Hq] (running max in log2 units, weight sum)
   void* out;
@@ -172,11 +170,7 @@ hipError_t launch_decode(const DecodeArgs& a, int D, hipStream_t s);
 hipError_t launch_put_bytes(void* dst, const void* src, size_t n, hipStream_t s);
 hipError_t launch_decode_merge(const MergeArgs& a, int D, hipStream_t s);
 hipError_t launch_prefill(const PrefillArgs& a, int D, hipStream_t s);
-// One launch of decode wave-path blocks followed by prefill blocks (mixed.hip; the decode's LDS-staged
-// prefix blocks are not part of it); the decode block count is padded to a multiple of 8 so each prefill
-// item keeps its planned XCD.
-hipError_t launch_mixed_step(const DecodeArgs& d, const PrefillArgs& p, int D, bool fp8, hipStream_t s);
-int mixed_step_decode_blocks(const DecodeArgs& d);
+hipError_t launch_prefill_long(const PrefillArgs& a, hipStream_t s);  // launch_prefill with long_items
 hipError_t launch_tier(const TierArgs& a, bool restore, hipStream_t s);
 hipError_t launch_block_hash(const HashArgs& a, int n_chunks, hipStream_t s);
 hipError_t launch_group_lcp(const GroupLcpArgs& a, int n_groups, hipStream_t s);

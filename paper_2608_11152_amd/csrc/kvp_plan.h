@@ -49,7 +49,7 @@ struct DecodePlan {
   int32_t group_reserved_blocks = 0;    // block slots the wave budget leaves to the shared-prefix path
 };
 
-// Prefill: one 4-wave workgroup per (session, kv head, 128-row query tile, key range).  The key range is
+// Prefill: one workgroup per (session, kv head, 256-row query tile, key range).  The key range is
 // a run of 64-key stages [st_lo, st_hi) (st_hi is clamped to the tile's own last stage); a tile whose
 // history is split over several workgroups writes one partial softmax state per range, merged per query
 // row by log-sum-exp afterwards.
@@ -63,6 +63,20 @@ struct PrefillItem {
   int32_t pad[2];
 };
 static_assert(sizeof(PrefillItem) == 32, "PrefillItem is uploaded as raw bytes");
+
+// An item as the kernels read it: the planner's item with what they would otherwise look up.
+struct PrefillWork {
+  int32_t seq, kvh, row0, st_lo;  // as in PrefillItem
+  int32_t nst;       // stages of the range (>= 1)
+  int32_t slot;      // as in PrefillItem
+  int32_t ctx;       // the session's cached length
+  int32_t q0;        // row of its first chunk token in q / out
+  int32_t nrows;     // its flattened query rows
+  int32_t n_keys;    // keys that any row of the tile sees
+  int32_t part0;     // split sessions: first partial (row r owns part0 + r * nsplit ..)
+  int32_t nsplit;    // key ranges per query row of the session
+};
+static_assert(sizeof(PrefillWork) == 48, "PrefillWork is uploaded as raw bytes");
 
 struct PrefillPlan {
   std::vector<PrefillItem> items;  // blockIdx order (XCD-aware, empty entries have seq = -1)
@@ -86,6 +100,10 @@ Status plan_decode(const int32_t* seq_lens, int B, int maxp, const kvp_group_pre
                    DecodePlan* plan, int chunk_start_pages = kChunkStartPages);
 Status plan_prefill(const int32_t* ctx_lens, const int32_t* cu_q, int B, int maxp, int Hq, int Hkv,
                     PrefillPlan* plan);
+// A plan's items as the kernels read them (ctx_lens, cu_q and G = Hq / Hkv as given to plan_prefill).
+std::vector<PrefillWork> prefill_work(const PrefillPlan& plan, const int32_t* ctx_lens, const int32_t* cu_q, int G);
+// Whether a plan's key ranges are long enough for the kernel that is made for them.
+bool prefill_items_long(const PrefillPlan& plan);
 Status check_tables(const int32_t* bt, int maxp, const int32_t* lens, int B, int num_pages,
                     const kvp_group_prefix* gp);
 
@@ -94,6 +112,10 @@ constexpr int kPrefillRows = 32 * kPrefillWaves;    // flattened query rows per 
 // A call whose tiles (x their 64-key stages) would not give about this many equal workgroups splits
 // tile histories into key ranges: the resident prefill workgroups of 256 CUs (8 waves per CU).
 constexpr int kPrefillSplitTarget = 256 * 8 / kPrefillWaves;
+// Items of at least this many stages on average go to the kernel for long key ranges (bf16 pages, d = 128).
+// Both sides measured, that kernel's time over the other's: 12.5 stages 1.05, 16: 1.01, 18: 0.99 (300-token chunks
+// over 2k: 36 stages 0.99), 20.5: 0.98, 32: 0.94, 64: 0.91-0.93, 130: 0.93, 1400: 0.91.
+constexpr int kPrefillLongStages = 18;
 constexpr int kPrefillMinSplitStages = 8;  // smallest key range of a split (512 keys)
 
 }  // namespace kvp

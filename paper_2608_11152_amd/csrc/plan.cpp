@@ -450,6 +450,29 @@ Status plan_prefill(const int32_t* ctx_lens, const int32_t* cu_q, int B, int max
   return {};
 }
 
+std::vector<PrefillWork> prefill_work(const PrefillPlan& plan, const int32_t* ctx_lens, const int32_t* cu_q, int G) {
+  std::vector<PrefillWork> work;
+  work.reserve(plan.items.size());
+  for (const PrefillItem& it : plan.items) {
+    if (it.seq < 0) {
+      work.push_back(PrefillWork{-1, 0, 0, 0, 0, -1, 0, 0, 0, 0, 0, 0});
+      continue;
+    }
+    const int i = it.seq, nrows = (cu_q[i + 1] - cu_q[i]) * G;
+    const int n_keys = ctx_lens[i] + std::min(nrows - 1, it.row0 + kPrefillRows - 1) / G + 1;
+    work.push_back(PrefillWork{i, it.kvh, it.row0, it.st_lo, std::min(it.st_hi, (n_keys + 63) / 64) - it.st_lo, it.slot,
+                               ctx_lens[i], cu_q[i], nrows, n_keys, plan.part_base[i], plan.nsplit[i]});
+  }
+  return work;
+}
+
+bool prefill_items_long(const PrefillPlan& plan) {
+  int64_t stages = 0;
+  for (const PrefillItem& it : plan.items)
+    if (it.seq >= 0) stages += it.st_hi - it.st_lo;
+  return stages >= (int64_t)kPrefillLongStages * plan.real_items;
+}
+
 Status check_tables(const int32_t* bt, int maxp, const int32_t* lens, int B, int num_pages,
                     const kvp_group_prefix* gp) {
   if (B > 0 && (!bt || !lens)) return fail(KVP_EINVAL, "NULL block table or lengths");

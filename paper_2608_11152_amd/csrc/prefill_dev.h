@@ -1,6 +1,4 @@
-// Device helpers of the chunked prefix prefill (one workgroup per (session, KV head, 128 flattened query
-// rows, key range) item; the workgroup body is prefill_body.inc).  Included by prefill.hip (the prefill
-// kernel) and mixed.hip (the mixed-step launch); everything here is inline.
+// Device helpers shared by the prefill kernels (prefill.hip, prefill_long.hip); everything here is inline.
 #pragma once
 
 #include "kvp_kernels.h"
@@ -30,7 +28,7 @@ __device__ __forceinline__ unsigned pack_bf16(float lo, float hi) {
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
-// FP8 pages (FP8 = true): a stage moves half the bytes from the pool and is converted exactly to bf16
+// FP8 pages: a stage moves half the bytes from the pool and is converted exactly to bf16
 // once, on its way into LDS; the matrix-core loop is the bf16 one.  The K scale is folded into the score
 // scale and the V scale into the output.
 __device__ __forceinline__ unsigned cvt_fp8x2(unsigned w, bool hi) {
@@ -41,20 +39,5 @@ __device__ __forceinline__ unsigned cvt_fp8x2(unsigned w, bool hi) {
 __device__ __forceinline__ u32x4 cvt8(unsigned w0, unsigned w1) {
   return u32x4{cvt_fp8x2(w0, false), cvt_fp8x2(w0, true), cvt_fp8x2(w1, false), cvt_fp8x2(w1, true)};
 }
-
-// LDS of one prefill workgroup: two stages of 4 pages (K and V blocks of one KV head, bf16).  The array is
-// a static of this function, so every kernel that calls it holds one copy.
-template <int D>
-struct PrefillLds {
-  static constexpr int bytes = 2 * 4 * 2 * 32 * D;
-};
-
-template <int D>
-__device__ __forceinline__ unsigned char* prefill_lds() {
-  __shared__ __attribute__((aligned(16))) unsigned char lds[PrefillLds<D>::bytes];
-  return lds;
-}
-
-
 }  // namespace pf
 }  // namespace kvp

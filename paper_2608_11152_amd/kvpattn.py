@@ -427,7 +427,7 @@ def mixed_step_workspace_size(pool: Pool, seq_lens, ctx_lens, cu_q, num_q_heads,
 
 def mixed_step_attn(pool: Pool, layer, q_dec, block_tables_dec, seq_lens, q_pf, block_tables_pf, ctx_lens, cu_q,
                     group_prefix=None, scale=None, out_dec=None, out_pf=None, out_dtype=None, ws=None, stream=None):
-    """paged_decode_attn and prefix_chunk_prefill_attn of one step in one launch.  Either part may be
+    """paged_decode_attn and prefix_chunk_prefill_attn of one step in one call.  Either part may be
     empty (q_dec with 0 rows / q_pf with 0 rows).  Returns (out_dec, out_pf)."""
     import torch
     sl, cl, cq = _i32(seq_lens), _i32(ctx_lens), _i32(cu_q)

@@ -1,0 +1,106 @@
+"""The prefill kernel for long key ranges at the edges of its pipeline: histories whose last 64-key stage holds
+1 to 64 keys, so that the number of 32-key halves is odd or even and the last page is partial; chunks of one
+row up to a whole tile; every GQA ratio; queries whose scores keep rising past the running max; a page id
+outside the pool.  Against float64 attention on the same bf16 values."""
+import math
+
+import numpy as np
+import pytest
+
+from gpu_helpers import MAX_ABS, MEAN_ABS, note
+from paper_2608_11152_amd import kvpattn as kp
+
+pytestmark = pytest.mark.gpu
+
+D = 128
+
+
+def _reference(q, k, v, ctx, scale):
+    """q [C, Hq, d], k and v [n, Hkv, d] bf16 on the device; row j sees keys [0, ctx + j]."""
+    import torch
+    C, Hq, _ = q.shape
+    Hkv = k.shape[1]
+    G = Hq // Hkv
+    out = torch.empty(q.shape, dtype=torch.float64, device=q.device)
+    hidden = torch.arange(k.shape[0], device=q.device)[None, :] > (ctx + torch.arange(C, device=q.device))[:, None]
+    for h in range(Hq):
+        s = (q[:, h].double() @ k[:, h // G].double().T.contiguous()) * scale
+        out[:, h] = torch.softmax(s.masked_fill(hidden, -math.inf), dim=1) @ v[:, h // G].double().contiguous()
+    return out
+
+
+# 256 (session, KV head) tiles: no history is split, each item has 40 stages or more.
+@pytest.mark.parametrize("G,Hkv,chunks", [(8, 8, [1, 2, 15, 16, 17, 31, 32]), (16, 8, [1, 3, 15, 16]),
+                                          (1, 8, [1, 63, 64, 65, 200, 256]), (2, 8, [1, 127, 128]),
+                                          (4, 8, [5, 33, 64])])
+@pytest.mark.parametrize("out_dtype", ["float32", "bfloat16"])
+def test_long_ranges(G, Hkv, chunks, out_dtype):
+    import torch
+    n_seq = 256 // Hkv
+    ctx = [2560 + x for x in ([0, 1, 15, 16, 17, 30, 31, 32, 33, 46, 47, 48, 49, 62, 63, 64] * 2)][:n_seq]
+    new = [chunks[i % len(chunks)] for i in range(n_seq)]
+    pages = [(a + b + 15) // 16 for a, b in zip(ctx, new)]
+    g = torch.Generator(device="cuda")
+    g.manual_seed(1000 * G + Hkv)
+    total = sum(pages)
+    perm = torch.randperm(total, generator=g, device="cuda").to(torch.int32)
+    k = torch.randn(total * 16, Hkv, D, generator=g, device="cuda").to(torch.bfloat16)
+    v = torch.randn(total * 16, Hkv, D, generator=g, device="cuda").to(torch.bfloat16)
+    q = torch.randn(sum(new), G * Hkv, D, generator=g, device="cuda").to(torch.bfloat16)
+    cu = np.concatenate([[0], np.cumsum(new)]).astype(np.int32)
+    for i in range(0, n_seq, 2):  # every other session: scores tens of powers of two apart
+        q[int(cu[i]):int(cu[i + 1])] *= 12
+    pool = kp.Pool(1, total, Hkv, D)
+    bt = torch.zeros(n_seq, max(pages), dtype=torch.int32, device="cuda")
+    at = 0
+    kp.kv_append(pool, 0, k, v, torch.arange(total, dtype=torch.int32, device="cuda")[None, :], [0], [0, total * 16])
+    for i, n in enumerate(pages):
+        bt[i, :n] = perm[at:at + n]
+        at += n
+    # stale slots past a session's end hold values that would show
+    note(f"long prefill G={G} Hkv={Hkv} chunks={chunks} {out_dtype}")
+    got = kp.prefix_chunk_prefill_attn(q, pool, 0, bt, ctx, cu, out_dtype=getattr(torch, out_dtype))
+    assert pool.device_error() == kp.KVP_OK
+    kp_, vp_ = k.view(total, 16, Hkv, D), v.view(total, 16, Hkv, D)
+    for i, (c, n) in enumerate(zip(ctx, new)):
+        ids = bt[i, :pages[i]].long()
+        ki, vi = (x[ids].view(-1, Hkv, D)[:c + n] for x in (kp_, vp_))
+        qi = q[int(cu[i]):int(cu[i + 1])]
+        err = (got[int(cu[i]):int(cu[i + 1])].double() - _reference(qi, ki, vi, c, 1 / math.sqrt(D))).abs()
+        # the scaled sessions' outputs are single values (|v| up to 5) rather than averages: bf16 weights and
+        # output round them by up to 2^-8 relative each
+        top = MAX_ABS if i % 2 else 5 * 2.0 ** -7
+        assert err.max() <= top and err.mean() <= (MEAN_ABS if i % 2 else top / 8), (i, c, n, err.max().item())
+    pool.close()
+
+
+def test_long_range_page_outside_the_pool():
+    """The page counts as zeros (keys and values), the call reports KVP_ERANGE, and stale values past the end of the
+    sequence (here infinities) do not reach the output."""
+    import torch
+    n, C, Hkv, G = 2565, 5, 8, 8
+    n_seq = 32
+    pages = (n + C + 15) // 16
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+    k = torch.randn(pages * 16, Hkv, D, generator=g, device="cuda").to(torch.bfloat16)
+    v = torch.randn(pages * 16, Hkv, D, generator=g, device="cuda").to(torch.bfloat16)
+    k[n + C:] = math.inf
+    v[n + C:] = math.nan
+    q = torch.randn(n_seq * C, G * Hkv, D, generator=g, device="cuda").to(torch.bfloat16)
+    pool = kp.Pool(1, pages, Hkv, D)
+    row = torch.arange(pages, dtype=torch.int32, device="cuda")
+    kp.kv_append(pool, 0, k, v, row[None, :], [0], [0, pages * 16])
+    bt = row[None, :].repeat(n_seq, 1).contiguous()
+    bt[3, 50] = pages  # one past the pool
+    note("long prefill with a page id outside the pool")
+    got = kp.prefix_chunk_prefill_attn(q, pool, 0, bt, [n] * n_seq, np.arange(n_seq + 1) * C)
+    assert pool.device_error() == kp.KVP_ERANGE
+    for i in (2, 3):
+        kk, vv = k[:n + C].clone(), v[:n + C].clone()
+        if i == 3:
+            kk[50 * 16:51 * 16] = 0
+            vv[50 * 16:51 * 16] = 0
+        err = (got[i * C:(i + 1) * C].double() - _reference(q[i * C:(i + 1) * C], kk, vv, n, 1 / math.sqrt(D))).abs()
+        assert err.max() <= MAX_ABS and err.mean() <= MEAN_ABS
+    pool.close()
