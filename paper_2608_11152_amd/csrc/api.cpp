@@ -577,7 +577,9 @@ kvp::PrefillArgs prefill_args(const PrefillLayout& L, kvp_pool_t pool, int layer
   a.maxp = maxp;
   a.items = reinterpret_cast<const kvp::PrefillWork*>(w + L.off_items);
   a.n_items = (int)L.plan.items.size();
-  a.long_items = pool->dtype == KVP_BF16 && pool->head_dim == 128 && kvp::prefill_items_long(L.plan);
+  const int64_t stages = kvp::prefill_mean_stages(L.plan);
+  a.long_items = pool->dtype == KVP_BF16 && pool->head_dim == 128 && stages >= kvp::kPrefillLongStages;
+  a.half_tiles = stages < kvp::kPrefillHalfTileStages;
   a.zero = reinterpret_cast<const unsigned char*>(pool->err) + kErrLine;
   a.part_acc = reinterpret_cast<float*>(w + L.off_acc);
   a.part_ml = reinterpret_cast<float2*>(w + L.off_ml);

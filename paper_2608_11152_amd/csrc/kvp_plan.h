@@ -102,8 +102,8 @@ Status plan_prefill(const int32_t* ctx_lens, const int32_t* cu_q, int B, int max
                     PrefillPlan* plan);
 // A plan's items as the kernels read them (ctx_lens, cu_q and G = Hq / Hkv as given to plan_prefill).
 std::vector<PrefillWork> prefill_work(const PrefillPlan& plan, const int32_t* ctx_lens, const int32_t* cu_q, int G);
-// Whether a plan's key ranges are long enough for the kernel that is made for them.
-bool prefill_items_long(const PrefillPlan& plan);
+// 64-key stages of a plan's items on average, rounded down.
+int64_t prefill_mean_stages(const PrefillPlan& plan);
 Status check_tables(const int32_t* bt, int maxp, const int32_t* lens, int B, int num_pages,
                     const kvp_group_prefix* gp);
 
@@ -116,6 +116,10 @@ constexpr int kPrefillSplitTarget = 256 * 8 / kPrefillWaves;
 // Both sides measured, that kernel's time over the other's: 12.5 stages 1.05, 16: 1.01, 18: 0.99 (300-token chunks
 // over 2k: 36 stages 0.99), 20.5: 0.98, 32: 0.94, 64: 0.91-0.93, 130: 0.93, 1400: 0.91.
 constexpr int kPrefillLongStages = 18;
+// In the other kernel, items of fewer stages than this on average get a workgroup per half tile (twice the
+// staging, but two workgroups on a CU overlap their starts and outputs).  Whole tiles' time over half tiles',
+// d = 128: 2 stages 1.12, 4.5: 1.04, 8 (36 items) 1.10, 8 (128 items) 1.00, 8.5: 0.99, FP8 pages 12.5: 0.99, 68: 0.94.
+constexpr int kPrefillHalfTileStages = 9;
 constexpr int kPrefillMinSplitStages = 8;  // smallest key range of a split (512 keys)
 
 }  // namespace kvp

@@ -466,11 +466,11 @@ std::vector<PrefillWork> prefill_work(const PrefillPlan& plan, const int32_t* ct
   return work;
 }
 
-bool prefill_items_long(const PrefillPlan& plan) {
+int64_t prefill_mean_stages(const PrefillPlan& plan) {
   int64_t stages = 0;
   for (const PrefillItem& it : plan.items)
     if (it.seq >= 0) stages += it.st_hi - it.st_lo;
-  return stages >= (int64_t)kPrefillLongStages * plan.real_items;
+  return stages / std::max<int64_t>(1, plan.real_items);
 }
 
 Status check_tables(const int32_t* bt, int maxp, const int32_t* lens, int B, int num_pages,

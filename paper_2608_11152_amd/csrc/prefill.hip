@@ -1,15 +1,20 @@
 // Chunked prefill of a new turn over a cached history (Eq. 1 of the paper: a later agentic turn only
 // prefills its L - H uncached tokens; they attend to the cached H tokens and causally to each other).
 //
-// Calls with short key ranges, FP8 pages or d = 64 (the others: prefill_long.hip).  One workgroup of
-// kPrefillWaves waves per (session, KV head, 32 x kPrefillWaves flattened query rows, key range).  Query rows
-// are flattened as position * G + head-in-group, so every K/V tile loaded serves all G query heads of its KV
-// head.  Keys stream through LDS in stages of 4 pages (64 keys), double-buffered: the next stage is loaded into
+// Calls with short key ranges, FP8 pages or d = 64 (the others: prefill_long.hip).  One workgroup of W waves
+// per (session, KV head, 32 W flattened query rows, key range): W = 8 takes an item, a tile of 256 rows, whole;
+// W = 4 gives each half of it a workgroup of its own, two to a CU.  Query rows are flattened as
+// position * G + head-in-group, so every K/V tile loaded serves all G query heads of its KV head.  Keys stream through LDS in stages of 4 pages (64 keys), double-buffered: the next stage is loaded into
 // registers while this stage's MFMA work runs, then stored to the other buffer.  Wave w owns 32 query
 // rows:
 //   S^T (64 keys x 32 rows) = K Q^T      v_mfma_f32_32x32x16_bf16, 2 key tiles x D/16 k-steps
 //   O^T (D x 32 rows)      += V^T P^T    the score tile's registers are the P^T operand (per page)
 // Masking is applied only to stages that reach past the wave's first query position (the diagonal).
+// What bounds short ranges: a workgroup's start (its item, page ids and first pages are dependent reads, its
+// queries come from HBM) and its output, which one workgroup per CU overlaps with nothing.  64 prompts of
+// 128-1024 tokens (about 6 stages an item) 394 us with output stores of 16-byte pieces, 364 us with whole lines
+// (286 us without queries and outputs); 64 prompts of 100 tokens 54 us, 44 us with whole lines, 39.5 us with
+// half-tile workgroups too.
 // A tile whose history the planner split into key ranges (few tiles over long histories) writes, per
 // range, the unnormalised partial state (running max, weight sum, accumulator) instead of its output;
 // the decode path's log-sum-exp merge kernel then combines the ranges of each query row.
@@ -20,8 +25,8 @@ namespace {
 
 using namespace pf;
 
-template <int D, bool FP8>
-__global__ __launch_bounds__(64 * kPrefillWaves, 8 / kPrefillWaves) void prefill_kernel(PrefillArgs a) {
+template <int D, bool FP8, int W>
+__global__ __launch_bounds__(64 * W, 8 / W) void prefill_kernel(PrefillArgs a) {
   constexpr int NS = D / 16;           // k-steps of the score product
   constexpr int NDT = D / 32;          // 32-row d tiles of the output
   constexpr int KB = 16 * D;           // elements per K (or V) block
@@ -30,25 +35,30 @@ __global__ __launch_bounds__(64 * kPrefillWaves, 8 / kPrefillWaves) void prefill
   constexpr int PBG = FP8 ? 2 * KB : PB;  // bytes per (page, head) block in the pool
   constexpr int NPG = 4;               // pages per stage
   constexpr int SB = NPG * PB;         // bytes per LDS stage
-  constexpr int NT = 64 * kPrefillWaves;  // threads of the workgroup
+  constexpr int NT = 64 * W;              // threads of the workgroup
   constexpr int RB = NT * 16;             // bytes one load round of the workgroup moves
   constexpr int NCH = NPG * PBG / RB;     // 16-byte pool pieces per thread per stage
   __shared__ __attribute__((aligned(16))) unsigned char lds[2 * SB];
 
-  const PrefillWork it = a.items[blockIdx.x];
-  if (it.seq < 0) return;
+  // W = 4: two workgroups per item, a tile half each, on the item's XCD (blocks 16k + x and 16k + 8 + x).
+  constexpr int PARTS = kPrefillWaves / W;
+  const int part = PARTS > 1 ? (blockIdx.x >> 3) % PARTS : 0;
+  const PrefillWork it = a.items[PARTS > 1 ? (blockIdx.x / (8 * PARTS)) * 8 + (blockIdx.x & 7) : blockIdx.x];
+  const int row0 = it.row0 + part * 32 * W;
+  if (it.seq < 0 || row0 >= it.nrows) return;
   const int tid = threadIdx.x, wv = tid >> 6, lane = tid & 63, l32 = lane & 31, g = lane >> 5;
   const int wvu = __builtin_amdgcn_readfirstlane(wv);  // the same value, known to be wave-uniform
   const int G = a.G;
-  const int ctx = it.ctx, q0 = it.q0, nrows = it.nrows, n_keys = it.n_keys;
-  const int f = it.row0 + wv * 32 + l32;  // this lane's query column (flattened row)
+  const int ctx = it.ctx, q0 = it.q0, nrows = it.nrows;
+  const int n_keys = ctx + min(nrows - 1, row0 + 32 * W - 1) / G + 1;  // keys any row of the workgroup sees
+  const int f = row0 + wv * 32 + l32;  // this lane's query column (flattened row)
   const bool row_ok = f < nrows;
   const int fpos = (row_ok ? f : nrows - 1) / G;
   const int hl = (row_ok ? f : nrows - 1) - fpos * G;
   const int qpos = ctx + fpos;
-  const int wave_min_pos = ctx + min(it.row0 + wv * 32, nrows - 1) / G;
+  const int wave_min_pos = ctx + min(row0 + wv * 32, nrows - 1) / G;
   const int n_pages = (n_keys + 15) / 16;
-  const int st_end = it.st_lo + it.nst;  // this workgroup's key range: stages [st_lo, st_end)
+  const int st_end = min(it.st_lo + it.nst, (n_keys + 63) / 64);  // this workgroup's key range: stages [st_lo, st_end)
 
   u32x4 qt[NS];
   {
@@ -308,40 +318,83 @@ __global__ __launch_bounds__(64 * kPrefillWaves, 8 / kPrefillWaves) void prefill
   }
   if (bad) atomicCAS(a.err, 0, KVP_ERANGE);
   l_run += __shfl_xor(l_run, 32);
-  if (!row_ok) return;
-  if (it.slot >= 0) {
-    // One key range of a split tile: the partial state of this query row, for the merge.
-    const int64_t pidx = (int64_t)it.part0 + (int64_t)fpos * it.nsplit + it.slot;
-    const int head = it.kvh * G + hl;
-    float* pa = a.part_acc + (pidx * a.Hq + head) * D + 4 * g;
+  // Output: a lane holds 4 consecutive dims of one row in every 8, which would go out in 16-byte pieces of 32
+  // rows per store.  The wave passes them through its own part of the stages' LDS (free after the last
+  // barrier; 16-byte chunks of a row are xor-ed with the row to spread the banks) and writes whole lines.
+  unsigned char* wl = lds + wv * (32 * 2 * D);
+  const int lgG = 31 - __builtin_clz(G);
+  constexpr int CH = D / 8;  // 16-byte chunks of a row of D bf16, or of half a row of floats
+  constexpr int RPI = 64 / CH;  // rows per store
+  const int c_out = lane % CH, r_out = lane / CH;
+  auto in_order = [&]() {
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  };
+  auto flush = [&](auto row_bytes, int off) {  // 32 rows of D * 2 bytes from LDS to row_bytes(row) + off
+    in_order();
 #pragma unroll
-    for (int d = 0; d < NDT; ++d)
+    for (int i = 0; i < 32 / RPI; ++i) {
+      const int r = i * RPI + r_out;
+      const int fr = row0 + wv * 32 + r;
+      const u32x4 v = ld16(wl + r * (2 * D) + ((c_out ^ (r & (CH - 1))) * 16));
+      if (fr < nrows) *reinterpret_cast<u32x4*>(row_bytes(fr) + off + c_out * 16) = v;
+    }
+    in_order();
+  };
+  if (it.slot >= 0 || a.out_f32) {
+    // floats: the output, or one key range's partial state of every query row for the merge
+    float* base = reinterpret_cast<float*>(it.slot >= 0 ? reinterpret_cast<void*>(a.part_acc) : a.out);
+    const float w = it.slot >= 0 ? a.v_scale : l_run > 0.0f ? a.v_scale / l_run : 0.0f;
+    auto row = [&](int fr) {
+      const int pos = fr >> lgG, head = it.kvh * G + (fr & (G - 1));
+      const int64_t r = it.slot >= 0 ? (int64_t)it.part0 + (int64_t)pos * it.nsplit + it.slot : (int64_t)q0 + pos;
+      return reinterpret_cast<unsigned char*>(base + (r * a.Hq + head) * D);
+    };
 #pragma unroll
-      for (int t4 = 0; t4 < 4; ++t4)
-        *reinterpret_cast<float4*>(pa + 32 * d + 8 * t4) =
-            make_float4(acc[d][4 * t4] * a.v_scale, acc[d][4 * t4 + 1] * a.v_scale, acc[d][4 * t4 + 2] * a.v_scale,
-                        acc[d][4 * t4 + 3] * a.v_scale);
-    if (g == 0) a.part_ml[pidx * a.Hq + head] = make_float2(m_run, l_run);
+    for (int hd = 0; hd < 2; ++hd) {
+#pragma unroll
+      for (int d = hd * (NDT / 2); d < (hd + 1) * (NDT / 2); ++d)
+#pragma unroll
+        for (int t4 = 0; t4 < 4; ++t4) {
+          const int ch = 8 * (d - hd * (NDT / 2)) + 2 * t4 + g;
+          *reinterpret_cast<float4*>(wl + l32 * (2 * D) + ((ch ^ (l32 & (CH - 1))) * 16)) =
+              make_float4(acc[d][4 * t4] * w, acc[d][4 * t4 + 1] * w, acc[d][4 * t4 + 2] * w, acc[d][4 * t4 + 3] * w);
+        }
+      flush(row, hd * 2 * D);
+    }
+    if (it.slot >= 0 && row_ok && g == 0)
+      a.part_ml[((int64_t)it.part0 + (int64_t)fpos * it.nsplit + it.slot) * a.Hq + it.kvh * G + hl] =
+          make_float2(m_run, l_run);
     return;
   }
   const float inv = l_run > 0.0f ? a.v_scale / l_run : 0.0f;
-  const int64_t o = ((int64_t)(q0 + fpos) * a.Hq + it.kvh * G + hl) * D + 4 * g;
 #pragma unroll
   for (int d = 0; d < NDT; ++d)
 #pragma unroll
     for (int t4 = 0; t4 < 4; ++t4) {
-      const int64_t oi = o + 32 * d + 8 * t4;
-      const float v0 = acc[d][4 * t4] * inv, v1 = acc[d][4 * t4 + 1] * inv;
-      const float v2 = acc[d][4 * t4 + 2] * inv, v3 = acc[d][4 * t4 + 3] * inv;
-      if (a.out_f32) {
-        *reinterpret_cast<float4*>(reinterpret_cast<float*>(a.out) + oi) = make_float4(v0, v1, v2, v3);
-      } else {
-        uint2 u;
-        u.x = pack_bf16(v0, v1);
-        u.y = pack_bf16(v2, v3);
-        *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(a.out) + oi) = u;
-      }
+      uint2 u;
+      u.x = pack_bf16(acc[d][4 * t4] * inv, acc[d][4 * t4 + 1] * inv);
+      u.y = pack_bf16(acc[d][4 * t4 + 2] * inv, acc[d][4 * t4 + 3] * inv);
+      *reinterpret_cast<uint2*>(wl + l32 * (2 * D) + (((4 * d + t4) ^ (l32 & (CH - 1))) * 16) + g * 8) = u;
     }
+  flush([&](int fr) {
+    return reinterpret_cast<unsigned char*>(reinterpret_cast<uint16_t*>(a.out) +
+                                            ((int64_t)(q0 + (fr >> lgG)) * a.Hq + it.kvh * G + (fr & (G - 1))) * D);
+  }, 0);
+}
+
+template <bool FP8>
+hipError_t launch_items(const PrefillArgs& a, int D, hipStream_t s) {
+  if (a.half_tiles) {
+    const dim3 grid((a.n_items + 7) / 8 * 16), block(256);
+    if (D == 128) hipLaunchKernelGGL((prefill_kernel<128, FP8, 4>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((prefill_kernel<64, FP8, 4>), grid, block, 0, s, a);
+  } else {
+    const dim3 grid(a.n_items), block(512);
+    if (D == 128) hipLaunchKernelGGL((prefill_kernel<128, FP8, 8>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((prefill_kernel<64, FP8, 8>), grid, block, 0, s, a);
+  }
+  return hipGetLastError();
 }
 
 }  // namespace
@@ -349,16 +402,7 @@ __global__ __launch_bounds__(64 * kPrefillWaves, 8 / kPrefillWaves) void prefill
 hipError_t launch_prefill(const PrefillArgs& a, int D, hipStream_t s) {
   if (a.n_items == 0) return hipSuccess;
   if (a.long_items) return launch_prefill_long(a, s);
-  const dim3 grid(a.n_items), block(64 * kPrefillWaves);
-  if (a.fp8) {
-    if (D == 128) hipLaunchKernelGGL((prefill_kernel<128, true>), grid, block, 0, s, a);
-    else hipLaunchKernelGGL((prefill_kernel<64, true>), grid, block, 0, s, a);
-  } else if (D == 128) {
-    hipLaunchKernelGGL((prefill_kernel<128, false>), grid, block, 0, s, a);
-  } else {
-    hipLaunchKernelGGL((prefill_kernel<64, false>), grid, block, 0, s, a);
-  }
-  return hipGetLastError();
+  return a.fp8 ? launch_items<true>(a, D, s) : launch_items<false>(a, D, s);
 }
 
 }  // namespace kvp
