@@ -930,25 +930,24 @@ int kvp_block_hashes(const int32_t* tokens, const int32_t* cu_tokens, int num_se
   if (pages == 0) return KVP_OK;
   if (!tokens || !hashes) return set_err(KVP_EINVAL, "tokens or hashes is NULL");
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
+  std::vector<int32_t> seq_first;
+  for (size_t k = 0; k < chunks.size(); ++k)
+    if (chunks[k].c == 0) seq_first.push_back((int32_t)k);
+  // pinned slot: [chunks | seq_first]
   Staging::Lease lease;
   const size_t nb = chunks.size() * sizeof(kvp::HashChunk);
-  int rc = staging().lease(nb, s, &lease);
+  int rc = staging().lease(nb + seq_first.size() * 4, s, &lease);
   if (rc) return rc;
-  std::memcpy(lease.host, chunks.data(), nb);
-  void* totals = nullptr;
-  hipError_t e = hipMallocAsync(&totals, chunks.size() * 16, s);
-  if (e != hipSuccess) {
-    (void)staging().release(lease);
-    return set_err(KVP_ENOMEM, "hipMallocAsync(%zu): %s", chunks.size() * 16, hipGetErrorString(e));
-  }
+  unsigned char* host = reinterpret_cast<unsigned char*>(lease.host);
+  std::memcpy(host, chunks.data(), nb);
+  std::memcpy(host + nb, seq_first.data(), seq_first.size() * 4);
   kvp::HashArgs a{};
   a.tokens = tokens;
-  a.chunks = reinterpret_cast<const kvp::HashChunk*>(lease.host);
+  a.chunks = reinterpret_cast<const kvp::HashChunk*>(host);
   a.seed = seed;
+  a.seq_first = reinterpret_cast<const int32_t*>(host + nb);
   a.out = hashes;
-  a.totals = reinterpret_cast<uint64_t*>(totals);
-  e = kvp::launch_block_hash(a, (int)chunks.size(), s);
-  (void)hipFreeAsync(totals, s);
+  const hipError_t e = kvp::launch_block_hash(a, (int)chunks.size(), (int)seq_first.size(), s);
   const int rr = staging().release(lease);
   if (e != hipSuccess) return hip_err(e, "kvp_block_hashes launch");
   return rr;
@@ -1108,24 +1107,16 @@ int kvp_prefix_lookup(kvp_prefix_table_t t, const uint64_t* hashes, const int32_
   rc = staging().lease(nb, s, &lease);
   if (rc) return rc;
   std::memcpy(lease.host, chunks.data(), nb);
-  void* scratch = nullptr;
-  hipError_t e = hipMallocAsync(&scratch, chunks.size() * 4, s);
-  if (e != hipSuccess) {
-    (void)staging().release(lease);
-    return set_err(KVP_ENOMEM, "hipMallocAsync(%zu): %s", chunks.size() * 4, hipGetErrorString(e));
-  }
   kvp::TableArgs a{};
   a.keys = t->keys;
   a.vals = t->vals;
   a.mask = t->mask;
   a.hashes = hashes;
   a.chunks = reinterpret_cast<const kvp::HashChunk*>(lease.host);
-  a.first_miss = reinterpret_cast<int32_t*>(scratch);
   a.matched = matched_pages;
   a.out_pages = page_ids;
   a.err = t->err;
-  e = kvp::launch_table(a, 2, (int)chunks.size(), s);
-  (void)hipFreeAsync(scratch, s);
+  const hipError_t e = kvp::launch_table(a, 2, (int)chunks.size(), s);
   const int rr = staging().release(lease);
   if (e != hipSuccess) return hip_err(e, "kvp_prefix_lookup launch");
   return rr;

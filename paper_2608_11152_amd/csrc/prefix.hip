@@ -13,11 +13,15 @@
 // independent 64-page chunks: pass 1 folds every page's tokens (one lane per page) and chains a chunk's
 // pages from 0 with an inclusive scan of the affine maps (a, b): h -> a*h + b; pass 2 composes the
 // chunk maps before each chunk to get its entering value and finishes every page.  A page's composed
-// slope is gamma^(j+1), known without data.
+// slope is gamma^(j+1), known without data, so a chunk's whole map is its length and its last page's value.
 //
 // A device hash table (open addressing, linear probing) maps a block hash to the physical page holding
 // that block, for the prefix lookup of new requests (probed 64 pages per wave, in two passes: per-chunk
-// probes, then the earliest miss of a sequence ends its reusable prefix).  Key 0 marks an empty slot, so a block hash of 0 is
+// probes, then the earliest miss of a sequence ends its reusable prefix).
+//
+// Both are bound by launches and dependent reads (4 MB of tokens in 5.6 us), so neither needs memory beyond its
+// output: pass 2 reads what it needs of the other chunks from there.  Scratch from the stream-ordered allocator
+// cost about 10 us of the host per call.  Key 0 marks an empty slot, so a block hash of 0 is
 // stored as 1; a slot's page is the largest page id inserted for its key, -1 once erased.
 #include "kvp_kernels.h"
 
@@ -38,11 +42,6 @@ __device__ __forceinline__ uint64_t shfl_up64(uint64_t v, int d) {
   return ((uint64_t)hi << 32) | lo;
 }
 
-__device__ __forceinline__ uint64_t shfl64(uint64_t v, int src) {
-  const unsigned lo = __shfl((unsigned)v, src), hi = __shfl((unsigned)(v >> 32), src);
-  return ((uint64_t)hi << 32) | lo;
-}
-
 __device__ __forceinline__ uint64_t table_key(uint64_t h) { return h ? h : 1ull; }
 
 // Inclusive scan over the 64 lanes of the affine maps h -> A*h + B (lane j ends with the composition of
@@ -59,8 +58,7 @@ __device__ __forceinline__ void affine_scan(uint64_t& A, uint64_t& B, int lane) 
 }
 
 // Pass 1: one wave per 64-page chunk.  Lane j folds its page's tokens; the scan gives the chunk-local
-// chain value B_j (the chain started from 0 at the chunk's first page), kept in the output slot, and the
-// chunk's whole map (gamma^n, B_{n-1}) for pass 2.
+// chain value B_j (the chain started from 0 at the chunk's first page), kept in the output slot.
 __global__ __launch_bounds__(64) void hash_chunk_kernel(HashArgs a) {
   const HashChunk ch = a.chunks[blockIdx.x];
   const int lane = threadIdx.x;
@@ -78,36 +76,77 @@ __global__ __launch_bounds__(64) void hash_chunk_kernel(HashArgs a) {
   }
   affine_scan(A, B, lane);
   if (lane < ch.n) a.out[ch.o0 + lane] = B;
-  if (lane == ch.n - 1) {
-    a.totals[2 * (ch.g0 + ch.c)] = A;
-    a.totals[2 * (ch.g0 + ch.c) + 1] = B;
-  }
 }
 
-// Pass 2: one wave per chunk.  The chain value entering chunk c is the composition of chunks 0..c-1
-// applied to the seed (scanned 64 chunks at a time); lane j then finishes
-// hash = mix(gamma^(j+1) * carry + B_j).
-__global__ __launch_bounds__(64) void hash_finish_kernel(HashArgs a) {
-  const HashChunk ch = a.chunks[blockIdx.x];
-  const int lane = threadIdx.x;
-  uint64_t carry = a.seed;
-  for (int c0 = 0; c0 < ch.c; c0 += 64) {
+__device__ __forceinline__ uint64_t gamma_pow(unsigned e) {  // by squaring
+  uint64_t g = 1, b = kGamma;
+  for (; e; e >>= 1) {
+    if (e & 1) g *= b;
+    b *= b;
+  }
+  return g;
+}
+
+// Pass 2: one 16-wave workgroup per sequence, kFinishChunks chunks at a time.  Thread i scans chunk i's map
+// (gamma^n, its last page's B) into the chain value entering the chunk; once all have read, the waves take the
+// chunks in turn and lane j finishes hash = mix(gamma^(j+1) * entering + B_j) in place.
+constexpr int kFinishChunks = 1024;
+constexpr int kFinishWaves = kFinishChunks / 64;
+
+__global__ __launch_bounds__(kFinishChunks) void hash_finish_kernel(HashArgs a) {
+  __shared__ uint64_t enter[kFinishChunks];
+  __shared__ uint64_t wave_a[kFinishWaves], wave_b[kFinishWaves];
+  const HashChunk first = a.chunks[a.seq_first[blockIdx.x]];  // a sequence's first chunk
+  const int nch = first.pad[0], np = first.pad[2];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  uint64_t* out = a.out + first.o0;
+  const uint64_t g_lane = gamma_pow((unsigned)lane + 1), g_chunk = gamma_pow(64);
+  uint64_t carry = a.seed;  // the chain value entering chunk c0
+  for (int c0 = 0; c0 < nch; c0 += kFinishChunks) {
+    const int c = c0 + (int)threadIdx.x;
+    const int n = min(64, np - 64 * c);  // chunk c's pages (<= 0 past the end)
     uint64_t A = 1, B = 0;
-    if (c0 + lane < ch.c) {
-      A = a.totals[2 * (ch.g0 + c0 + lane)];
-      B = a.totals[2 * (ch.g0 + c0 + lane) + 1];
+    if (n > 0) {
+      A = n == 64 ? g_chunk : gamma_pow((unsigned)n);
+      B = out[64 * (int64_t)c + n - 1];
     }
     affine_scan(A, B, lane);
-    const int last = min(63, ch.c - c0 - 1);
-    carry = shfl64(A, last) * carry + shfl64(B, last);
-  }
-  if (lane < ch.n) {
-    uint64_t g = 1, b = kGamma;  // gamma^(lane + 1) by squaring
-    for (unsigned e = (unsigned)lane + 1; e; e >>= 1) {
-      if (e & 1) g *= b;
-      b *= b;
+    if (lane == 63) {
+      wave_a[w] = A;
+      wave_b[w] = B;
     }
-    a.out[ch.o0 + lane] = mix64(g * carry + a.out[ch.o0 + lane]);
+    __syncthreads();
+    uint64_t ha = 1, hb = 0;  // the maps of the waves before this one, composed
+    uint64_t ta = 1, tb = 0;  // and of all of them
+    for (int k = 0; k < kFinishWaves; ++k) {
+      if (k == w) {
+        ha = ta;
+        hb = tb;
+      }
+      tb = tb * wave_a[k] + wave_b[k];
+      ta = ta * wave_a[k];
+    }
+    // entering chunk c: the chunks before it in the wave (lane - 1's inclusive scan) after those waves
+    const uint64_t pa = shfl_up64(A, 1), pb = shfl_up64(B, 1);
+    const uint64_t at_wave = ha * carry + hb;
+    enter[threadIdx.x] = lane == 0 ? at_wave : pa * at_wave + pb;
+    carry = ta * carry + tb;
+    __syncthreads();
+    const int here = min(kFinishChunks, nch - c0);
+    for (int k0 = w; k0 < here; k0 += 4 * kFinishWaves) {
+      uint64_t v[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int64_t p = 64 * (int64_t)(c0 + k0 + u * kFinishWaves) + lane;
+        if (k0 + u * kFinishWaves < here && p < np) v[u] = out[p];
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int64_t p = 64 * (int64_t)(c0 + k0 + u * kFinishWaves) + lane;
+        if (k0 + u * kFinishWaves < here && p < np) out[p] = mix64(g_lane * enter[k0 + u * kFinishWaves] + v[u]);
+      }
+    }
+    __syncthreads();
   }
 }
 
@@ -186,32 +225,43 @@ __device__ __forceinline__ int table_find(const TableArgs& a, uint64_t h) {
   return -1;
 }
 
-// Lookup pass 1: one wave per 64-page chunk of a sequence.  Every page is probed; the chunk's first
-// miss (a page index within the sequence, or the sequence's page count when it has none) goes to
-// scratch.
+// Lookup pass 1: one wave per 64-page chunk of a sequence.  Every page is probed; the pages from the chunk's
+// first miss on are reported as -1, so a chunk has a miss if its last page is -1.
 __global__ __launch_bounds__(64) void lookup_chunk_kernel(TableArgs a) {
   const HashChunk ch = a.chunks[blockIdx.x];
   const int lane = threadIdx.x;
   int page = -1;
   if (lane < ch.n) page = table_find(a, a.hashes[ch.o0 + lane]);
-  if (lane < ch.n) a.out_pages[ch.o0 + lane] = page;
   const uint64_t miss = __ballot(lane < ch.n && page < 0);
-  if (lane == 0) a.first_miss[ch.g0 + ch.c] = miss ? 64 * ch.c + (int)__builtin_ctzll(miss) : ch.pad[2];
+  if (miss && lane >= (int)__builtin_ctzll(miss)) page = -1;
+  if (lane < ch.n) a.out_pages[ch.o0 + lane] = page;
 }
 
-// Lookup pass 2: one wave per chunk.  The sequence's reusable prefix ends at the earliest first miss of
-// its chunks; pages from there on are reported as -1.
+// Lookup pass 2: one wave per chunk.  The sequence's reusable prefix ends at the earliest miss of its chunks: a
+// chunk behind one that has a miss is reported as -1 (which other waves may see early: such a chunk lies behind
+// the earliest miss as well), and the first chunk's wave reports the prefix's length.
 __global__ __launch_bounds__(64) void lookup_finish_kernel(TableArgs a) {
   const HashChunk ch = a.chunks[blockIdx.x];
   const int lane = threadIdx.x;
-  const int nch = ch.pad[0];
-  int m = 1 << 30;
-  for (int c0 = 0; c0 < nch; c0 += 64)
-    if (c0 + lane < nch) m = min(m, a.first_miss[ch.g0 + c0 + lane]);
-#pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) m = min(m, __shfl_xor(m, d));
-  if (lane < ch.n && 64 * ch.c + lane >= m) a.out_pages[ch.o0 + lane] = -1;
-  if (ch.c == 0 && lane == 0) a.matched[ch.pad[1]] = m;
+  const int nch = ch.pad[0], np = ch.pad[2];
+  int32_t* out = a.out_pages + (ch.o0 - 64 * ch.c);  // the sequence's first page
+  const int upto = ch.c == 0 ? nch : ch.c;
+  int missing = -1;  // the earliest of chunks 0 .. upto - 1 with a miss
+  for (int c0 = 0; c0 < upto && missing < 0 && np > 0; c0 += 64) {
+    const int c = c0 + lane;
+    const uint64_t m = __ballot(c < upto && out[min(64 * c + 63, np - 1)] < 0);
+    if (m) missing = c0 + (int)__builtin_ctzll(m);
+  }
+  if (ch.c > 0) {
+    if (missing >= 0 && lane < ch.n) a.out_pages[ch.o0 + lane] = -1;
+    return;
+  }
+  int matched = np;
+  if (missing >= 0) {
+    const int p = 64 * missing + lane;
+    matched = 64 * missing + (int)__builtin_ctzll(__ballot(p < np && out[p] < 0));
+  }
+  if (lane == 0) a.matched[ch.pad[1]] = matched;
 }
 
 __global__ void fill_table_kernel(uint64_t* keys, int32_t* vals, int64_t n) {
@@ -224,12 +274,12 @@ __global__ void fill_table_kernel(uint64_t* keys, int32_t* vals, int64_t n) {
 
 }  // namespace
 
-hipError_t launch_block_hash(const HashArgs& a, int n_chunks, hipStream_t s) {
+hipError_t launch_block_hash(const HashArgs& a, int n_chunks, int n_seqs, hipStream_t s) {
   if (n_chunks == 0) return hipSuccess;
   hipLaunchKernelGGL(hash_chunk_kernel, dim3(n_chunks), dim3(64), 0, s, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(hash_finish_kernel, dim3(n_chunks), dim3(64), 0, s, a);
+  hipLaunchKernelGGL(hash_finish_kernel, dim3(n_seqs), dim3(kFinishChunks), 0, s, a);
   return hipGetLastError();
 }
 
