@@ -159,6 +159,8 @@ def _alloc_on(stream, shape, dtype, device):
     """A buffer the kernels enqueued on `stream` write or read: allocated in that stream's context, so the
     caching allocator does not hand its memory to another stream's allocation while the work is pending."""
     import torch
+    if stream is None:  # the current stream: its context is the one we are in (entering it again costs 10 us)
+        return torch.empty(shape, dtype=dtype, device=device)
     with torch.cuda.stream(_torch_stream(stream)):
         return torch.empty(shape, dtype=dtype, device=device)
 
