@@ -73,8 +73,9 @@ int hip_err(hipError_t e, const char* what) {
 // Pieces are cut from blocks, each open for one stream; a block that has no room for the next piece is closed
 // by recording one event behind its work, and is used again once the event has completed.  An event behind
 // every call costs the stream a 5.6 us gap before its next kernel (kernel trace; no gap between kernels
-// without one): mixed decode 371.8 -> 369.1 us, RLHF 180.2 -> 177.2 us, a 67 MB append 20.7 -> 17.2 us without.  Blocks open for a stream that has gone quiet are not reused (nothing was recorded
-// behind their work), so at most kMaxOpen of them stay open: past that every release closes its block.
+// without one): mixed decode 371.8 -> 369.1 us, RLHF 180.2 -> 177.2 us, a 67 MB append 20.7 -> 17.2 us
+// without.  Blocks open for a stream that has gone quiet are not reused (nothing was recorded behind their
+// work), so at most kMaxOpen of them stay open: past that every release closes its block.
 class Staging {
  public:
   struct Lease {
@@ -406,7 +407,11 @@ int lease_runs(const std::vector<kvp::PageRun>& runs, hipStream_t s, Staging::Le
 struct DecodeLayout {
   kvp::DecodePlan plan;
   std::vector<int32_t> merge_info;  // one 16-byte record per merged sequence: {seq, first partial, count, 0}
-  size_t off_wave = 0, off_seg = 0, off_group = 0, off_members = 0, off_part_base = 0, off_merge = 0;
+  int rec_members = 1;              // member entries of a wave-path record
+  size_t rec_bytes() const {
+    return (sizeof(kvp::DecodeRec) + sizeof(kvp::DecodeRec::Member) * (rec_members - 1) + 15) & ~size_t(15);
+  }
+  size_t off_wave = 0, off_group = 0, off_members = 0, off_part_base = 0, off_merge = 0;
   int max_parts = 0;                // largest partial count of a merged sequence
   size_t meta_bytes = 0;            // work list bytes (offsets above, 256-byte aligned)
   size_t off_acc = 0, off_ml = 0, total = 0;
@@ -416,8 +421,26 @@ struct DecodeLayout {
     auto put = [&](size_t off, const void* src, size_t n) {
       if (n) std::memcpy(dst + off, src, n);
     };
-    put(off_wave, plan.wave_items.data(), plan.wave_items.size() * sizeof(kvp::DecodeItem));
-    put(off_seg, plan.seg_off.data(), plan.seg_off.size() * 4);
+    // Wave-path records: segment s's first chunk is record s, its further chunks follow all the first ones.
+    const int segs = (int)plan.seg_off.size() - 1;
+    const size_t stride = rec_bytes();
+    unsigned char* const recs = dst + off_wave;
+    const kvp::DecodeItem* it = plan.wave_items.data();
+    const int32_t *seg_off = plan.seg_off.data(), *members = plan.members.data(), *part_base = plan.part_base.data();
+    int32_t tail = segs;
+    for (int s = 0, c = 0; s < segs; ++s) {
+      const int c1 = seg_off[s + 1];
+      for (int32_t at = s; c < c1; ++c, ++it) {
+        const int32_t next = c + 1 < c1 ? tail++ : -1;
+        auto* rec = reinterpret_cast<kvp::DecodeRec*>(recs + at * stride);
+        const int n_mem = it->n_mem, slot = it->slot;
+        const int32_t* mem = members + it->mem_off;
+        *rec = {it->row, it->page_lo, it->page_hi, it->tok_end, it->kind << 16 | n_mem, next,
+                {{mem[0], slot < 0 ? -1 : part_base[mem[0]] + slot}}};
+        for (int m = 1; m < n_mem; ++m) rec->mem[m] = {mem[m], slot < 0 ? -1 : part_base[mem[m]] + slot};
+        at = next;
+      }
+    }
     put(off_group, plan.group_items.data(), plan.group_items.size() * sizeof(kvp::DecodeItem));
     put(off_members, plan.members.data(), plan.members.size() * 4);
     put(off_part_base, plan.part_base.data(), plan.part_base.size() * 4);
@@ -447,8 +470,8 @@ int layout_decode(kvp_pool_t pool, const int32_t* seq_lens, int B, int maxp, con
     at = (at + n + 255) & ~size_t(255);
     return off;
   };
-  L->off_wave = slot(P.wave_items.size() * sizeof(kvp::DecodeItem));
-  L->off_seg = slot(P.seg_off.size() * 4);
+  for (const kvp::DecodeItem& it : P.wave_items) L->rec_members = std::max(L->rec_members, it.n_mem);
+  L->off_wave = slot(P.wave_items.size() * L->rec_bytes());
   L->off_group = slot(P.group_items.size() * sizeof(kvp::DecodeItem));
   L->off_members = slot(P.members.size() * 4);
   L->off_part_base = slot(P.part_base.size() * 4);
@@ -485,8 +508,9 @@ kvp::DecodeArgs decode_args(const DecodeLayout& L, kvp_pool_t pool, int layer, c
   a.scale_log2 = scale * 1.4426950408889634f * (a.fp8 ? pool->k_scale[layer] : 1.0f);
   a.v_scale = a.fp8 ? pool->v_scale[layer] : 1.0f;
   a.err = pool->err;
-  a.items = reinterpret_cast<const kvp::DecodeItem*>(meta + L.off_wave);
-  a.seg_off = reinterpret_cast<const int32_t*>(meta + L.off_seg);
+  a.recs = meta + L.off_wave;
+  a.rec_bytes = (int)L.rec_bytes();
+  a.rec_members = L.rec_members;
   a.n_items = (int)P.seg_off.size() - 1;
   a.group_items = reinterpret_cast<const kvp::DecodeItem*>(meta + L.off_group);
   a.n_group_items = (int)P.group_items.size();
@@ -497,8 +521,8 @@ kvp::DecodeArgs decode_args(const DecodeLayout& L, kvp_pool_t pool, int layer, c
 
 // The merge of split partials (decode: one record per split sequence; prefill: one per query row of a
 // split session), enqueued after the kernels that write the partials.
-hipError_t launch_merge(const int32_t* merge_info, int n_merge, int max_parts, const float* part_acc, const float2* part_ml,
-                        void* out, int out_f32, int num_q_heads, kvp_pool_t pool, hipStream_t s) {
+hipError_t launch_merge(const int32_t* merge_info, int n_merge, int max_parts, const float* part_acc,
+                        const float2* part_ml, void* out, int out_f32, int num_q_heads, kvp_pool_t pool, hipStream_t s) {
   if (n_merge == 0) return hipSuccess;
   kvp::MergeArgs mg{};
   mg.merge_info = merge_info;

@@ -116,11 +116,11 @@ __device__ __forceinline__ void report_group_mismatch(const DecodeArgs& a, bool 
   if (__any(differs) && lane == 0) atomicCAS(a.err, 0, KVP_EGROUP);
 }
 
-// Store one column's state: normalised output (slot < 0) or a partial for the merge kernel.
+// Store one column's state: normalised output (part < 0) or partial `part` for the merge kernel.
 template <int D, int NT>
-__device__ __forceinline__ void write_state(const DecodeArgs& a, const DecodeItem& it, const SoftState<NT>& st,
-                                            int seq, int head, int q4) {
-  if (it.slot < 0) {
+__device__ __forceinline__ void write_state(const DecodeArgs& a, int64_t part, const SoftState<NT>& st, int seq,
+                                            int head, int q4) {
+  if (part < 0) {
     const float inv = st.l > 0.0f ? a.v_scale / st.l : 0.0f;
     const int64_t o = ((int64_t)seq * a.Hq + head) * D + 4 * q4;
 #pragma unroll
@@ -136,13 +136,17 @@ __device__ __forceinline__ void write_state(const DecodeArgs& a, const DecodeIte
       }
     }
   } else {
-    const int64_t pidx = (int64_t)a.part_base[seq] + it.slot;
-    float* pa = a.part_acc + (pidx * a.Hq + head) * D + 4 * q4;
+    float* pa = a.part_acc + (part * a.Hq + head) * D + 4 * q4;
 #pragma unroll
     for (int d = 0; d < NT; ++d) *reinterpret_cast<f32x4*>(pa + 16 * d) = st.acc[d] * a.v_scale;
-    if (q4 == 0) a.part_ml[pidx * a.Hq + head] = make_float2(st.m, st.l);
+    if (q4 == 0) a.part_ml[part * a.Hq + head] = make_float2(st.m, st.l);
   }
 }
+
+// A wave-path chunk as one lane sees it: seq and part are those of the member that owns the lane's query column.
+struct WaveChunk {
+  int row, page_lo, page_hi, tok_end, kind, n_mem, seq, part;
+};
 
 // ---------------------------------------------------------------------------------------------------
 // One wave per (item, KV head): private page ranges, and shared-prefix ranges of groups with <= 16
@@ -150,7 +154,7 @@ __device__ __forceinline__ void write_state(const DecodeArgs& a, const DecodeIte
 // D/16 V loads of 16 bytes per lane (16 KB per wave at d = 128).
 // ---------------------------------------------------------------------------------------------------
 template <int D>
-__device__ __forceinline__ void decode_wave_chunk(const DecodeArgs& a, const DecodeItem& it, int kvh, int lane) {
+__device__ __forceinline__ void decode_wave_chunk(const DecodeArgs& a, const WaveChunk& it, int kvh, int lane) {
   constexpr int NS = D / 32;
   constexpr int NT = D / 16;
   constexpr int KB = 16 * D;
@@ -159,9 +163,8 @@ __device__ __forceinline__ void decode_wave_chunk(const DecodeArgs& a, const Dec
   const bool col_ok = c16 < ncols;
   int seq = 0, head = 0;
   if (col_ok) {
-    const int m = c16 / a.G;
-    seq = a.members[it.mem_off + m];
-    head = kvh * a.G + (c16 - m * a.G);
+    seq = it.seq;
+    head = kvh * a.G + c16 % a.G;
   }
   u32x4 qt[NS];
   {
@@ -220,7 +223,7 @@ __device__ __forceinline__ void decode_wave_chunk(const DecodeArgs& a, const Dec
   report_group_mismatch(a, differs, lane);
   st.l += __shfl_xor(st.l, 16);
   st.l += __shfl_xor(st.l, 32);
-  if (col_ok) write_state<D, NT>(a, it, st, seq, head, q4);
+  if (col_ok) write_state<D, NT>(a, it.part, st, seq, head, q4);
 }
 
 // ---------------------------------------------------------------------------------------------------
@@ -359,7 +362,7 @@ __device__ __forceinline__ void decode_group_block(const DecodeArgs& a, int bloc
   st.l += __shfl_xor(st.l, 16);
   st.l += __shfl_xor(st.l, 32);
   if (!col_ok) return;
-  write_state<D, NT>(a, it, st, seq, head, q4);
+  write_state<D, NT>(a, it.slot < 0 ? -1 : (int64_t)a.part_base[seq] + it.slot, st, seq, head, q4);
 }
 
 // ---------------------------------------------------------------------------------------------------
@@ -403,7 +406,7 @@ __device__ __forceinline__ void fp8_substep(SoftState<NT>& st, const u32x4 (&qt)
 }
 
 template <int D>
-__device__ __forceinline__ void decode_wave_chunk_fp8(const DecodeArgs& a, const DecodeItem& it, int kvh, int lane) {
+__device__ __forceinline__ void decode_wave_chunk_fp8(const DecodeArgs& a, const WaveChunk& it, int kvh, int lane) {
   constexpr int NS = D / 32;
   constexpr int NT = D / 16;
   constexpr int KB = 16 * D;  // bytes per K (or V) block
@@ -412,9 +415,8 @@ __device__ __forceinline__ void decode_wave_chunk_fp8(const DecodeArgs& a, const
   const bool col_ok = c16 < ncols;
   int seq = 0, head = 0;
   if (col_ok) {
-    const int m = c16 / a.G;
-    seq = a.members[it.mem_off + m];
-    head = kvh * a.G + (c16 - m * a.G);
+    seq = it.seq;
+    head = kvh * a.G + c16 % a.G;
   }
   u32x4 qt[NS];
   {
@@ -487,7 +489,7 @@ __device__ __forceinline__ void decode_wave_chunk_fp8(const DecodeArgs& a, const
   report_group_mismatch(a, differs, lane);
   st.l += __shfl_xor(st.l, 16);
   st.l += __shfl_xor(st.l, 32);
-  if (col_ok) write_state<D, NT>(a, it, st, seq, head, q4);
+  if (col_ok) write_state<D, NT>(a, it.part, st, seq, head, q4);
 }
 
 template <int D>
@@ -620,7 +622,7 @@ __device__ __forceinline__ void decode_group_block_fp8(const DecodeArgs& a, int 
   st.l += __shfl_xor(st.l, 16);
   st.l += __shfl_xor(st.l, 32);
   if (!col_ok) return;
-  write_state<D, NT>(a, it, st, seq, head, q4);
+  write_state<D, NT>(a, it.slot < 0 ? -1 : (int64_t)a.part_base[seq] + it.slot, st, seq, head, q4);
 }
 
 // ---------------------------------------------------------------------------------------------------
@@ -636,11 +638,19 @@ __device__ __forceinline__ void decode_wave_block(const DecodeArgs& a, int block
   const int seg = wid / a.Hkv;
   const int kvh = wid - seg * a.Hkv;
   if (seg >= a.n_items) return;
-  const int c1 = a.seg_off[seg + 1];
-  for (int c = a.seg_off[seg]; c < c1; ++c) {
-    if constexpr (FP8) decode_wave_chunk_fp8<D>(a, a.items[c], kvh, lane);
-    else decode_wave_chunk<D>(a, a.items[c], kvh, lane);
-  }
+  // the member that owns this lane's query column (columns past the chunk's members are masked by col_ok)
+  const int m = min((lane & 15) / a.G, a.rec_members - 1);
+  int r = seg;
+  do {
+    const unsigned char* rec = a.recs + (int64_t)r * a.rec_bytes;
+    const int4 lo = *reinterpret_cast<const int4*>(rec);
+    const int2 hi = *reinterpret_cast<const int2*>(rec + 16);
+    const int2 member = *reinterpret_cast<const int2*>(rec + offsetof(DecodeRec, mem) + 8 * m);
+    const WaveChunk it{lo.x, lo.y, lo.z, lo.w, hi.x >> 16, hi.x & 0xffff, member.x, member.y};
+    if constexpr (FP8) decode_wave_chunk_fp8<D>(a, it, kvh, lane);
+    else decode_wave_chunk<D>(a, it, kvh, lane);
+    r = hi.y;
+  } while (r >= 0);
 }
 
 }  // namespace dec

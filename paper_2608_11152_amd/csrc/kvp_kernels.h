@@ -44,14 +44,31 @@ struct GatherArgs {
   float scale_k, scale_v;
 };
 
+// A wave-path chunk as the kernel reads it, over the bus from pinned host memory: all that a wave needs before its
+// first page in one record, so that a chunk starts after one such read.  The segment's chunk range, the item and
+// its member list were three dependent reads of 1.3 us each (and the partial index a fourth, at the chunk's end):
+// one sequence of 131,007 tokens 57.9 -> 55.5 us, RLHF 177.3 -> 175.0 us, 9 groups over short prompts 28.1 ->
+// 23.9 us.  A record holds the same number of members throughout a call (the most that a chunk has).
+struct DecodeRec {
+  int32_t row, page_lo, page_hi, tok_end;  // as in DecodeItem
+  int32_t kind_mem;           // kind << 16 | n_mem
+  int32_t next;               // record of the segment's next chunk, -1 = none
+  struct Member {
+    int32_t seq;
+    int32_t part;             // index of the member's partial, -1 = write the output
+  } mem[1];
+};
+static_assert(sizeof(DecodeRec) == 32, "two 16-byte reads, of which the last holds the first member");
+
 struct DecodeArgs {
   const uint16_t* q;        // [B, Hq, D] bf16
   const uint16_t* layer;
   const int32_t* bt;
   int maxp;
-  const DecodeItem* items;    // wave path: chunks in segment order
+  const unsigned char* recs;  // wave path: one DecodeRec per chunk, segment s starting at record s
+  int rec_bytes;              // bytes from one record to the next
+  int rec_members;            // member entries of a record
   int n_items;                // wave path: segment count
-  const int32_t* seg_off;     // wave path: [segments + 1] chunk offsets
   const DecodeItem* group_items;  // shared-prefix path (LDS-staged, > 16 query columns)
   int n_group_items;
   int n_group_blocks;         // n_group_items * Hkv

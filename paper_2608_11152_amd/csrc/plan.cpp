@@ -166,11 +166,10 @@ Status plan_decode(const int32_t* seq_lens, int B, int maxp, const kvp_group_pre
   int64_t seg_pages = (total_pages + segs_target - 1) / segs_target;
   seg_pages = std::max<int64_t>(kMinSegmentPages, (seg_pages + 1) & ~int64_t(1));
 
-  struct Chunk { int unit, lo, hi; };
+  struct Chunk { int unit, lo, hi, k; };  // k: number among its unit's chunks
   std::vector<Chunk> wave_chunks;
-  std::vector<int> seg_of_chunk;
   wave_chunks.reserve(wave_units.size() + segs_target + 1);
-  seg_of_chunk.reserve(wave_units.size() + segs_target + 1);
+  plan->seg_off.reserve(segs_target + 2);
   std::vector<int> n_chunks_wave(wave_units.size(), 0);
   {
     // A chunk's start costs a wave about chunk_start_pages pages of streaming (its item, the query
@@ -184,6 +183,12 @@ Status plan_decode(const int32_t* seq_lens, int B, int maxp, const kvp_group_pre
       for (size_t u = 0; u < wave_units.size(); ++u) {
         int lo = wave_units[u].lo;
         while (lo < wave_units[u].hi) {
+          if (!emit && fill == 0) {  // whole segments of one chunk each, counted at once
+            const int64_t full = (wave_units[u].hi - lo) / (cap - K);
+            seg += (int)full;
+            lo += (int)(full * (cap - K));
+            if (lo == wave_units[u].hi) break;
+          }
           if (fill > 0 && fill + K >= cap) {  // no room for another start and a page
             fill = 0;
             ++seg;
@@ -191,9 +196,8 @@ Status plan_decode(const int32_t* seq_lens, int B, int maxp, const kvp_group_pre
           fill += K;
           const int take = (int)std::min<int64_t>(wave_units[u].hi - lo, cap - fill);
           if (emit) {
-            wave_chunks.push_back(Chunk{(int)u, lo, lo + take});
-            seg_of_chunk.push_back(seg);
-            n_chunks_wave[u]++;
+            if (seg == (int)plan->seg_off.size()) plan->seg_off.push_back((int)wave_chunks.size());
+            wave_chunks.push_back(Chunk{(int)u, lo, lo + take, n_chunks_wave[u]++});
           }
           lo += take;
           fill += take;
@@ -216,6 +220,7 @@ Status plan_decode(const int32_t* seq_lens, int B, int maxp, const kvp_group_pre
       cap = hi;
     }
     cut(cap, true);
+    plan->seg_off.push_back((int)wave_chunks.size());  // {0} without a chunk
     plan->pages_per_split = (int)(cap - K);
   }
   // Wide shared-prefix units (LDS-staged workgroup kernel): fixed chunks of kGroupChunkPages pages.
@@ -223,8 +228,8 @@ Status plan_decode(const int32_t* seq_lens, int B, int maxp, const kvp_group_pre
   std::vector<int> n_chunks_group(group_units.size(), 0);
   for (size_t u = 0; u < group_units.size(); ++u)
     for (int lo = group_units[u].lo; lo < group_units[u].hi; lo += kGroupChunkPages) {
-      group_chunks.push_back(Chunk{(int)u, lo, std::min(group_units[u].hi, lo + kGroupChunkPages)});
-      n_chunks_group[u]++;
+      group_chunks.push_back(
+          Chunk{(int)u, lo, std::min(group_units[u].hi, lo + kGroupChunkPages), n_chunks_group[u]++});
     }
 
   // Partial slots: per sequence, its shared-prefix chunks first (the same slot index for every member
@@ -252,29 +257,16 @@ Status plan_decode(const int32_t* seq_lens, int B, int maxp, const kvp_group_pre
   }
   plan->total_parts = total;
 
-  auto emit = [&](const Unit& un, const Chunk& c, int k) {
+  auto emit = [&](const Unit& un, const Chunk& c) {
     DecodeItem it{un.kind, un.row, c.lo, c.hi, un.tok_end, un.mem_off, un.n_mem, 0};
-    if (un.kind == 1) it.slot = k;
-    else it.slot = (n_prefix[un.row] == 0 && n_priv[un.row] == 1) ? -1 : n_prefix[un.row] + k;
+    if (un.kind == 1) it.slot = c.k;
+    else it.slot = (n_prefix[un.row] == 0 && n_priv[un.row] == 1) ? -1 : n_prefix[un.row] + c.k;
     return it;
   };
-  {
-    std::vector<int> k_of(wave_units.size(), 0);
-    plan->seg_off.reserve(segs_target + 2);
-    plan->wave_items.reserve(wave_chunks.size());
-    plan->seg_off.push_back(0);
-    for (size_t c = 0; c < wave_chunks.size(); ++c) {
-      if (c > 0 && seg_of_chunk[c] != seg_of_chunk[c - 1]) plan->seg_off.push_back((int)c);
-      const int u = wave_chunks[c].unit;
-      plan->wave_items.push_back(emit(wave_units[u], wave_chunks[c], k_of[u]++));
-    }
-    plan->seg_off.push_back((int)wave_chunks.size());
-    if (wave_chunks.empty()) plan->seg_off.assign(1, 0);
-  }
-  {
-    std::vector<int> k_of(group_units.size(), 0);
-    for (const Chunk& c : group_chunks) plan->group_items.push_back(emit(group_units[c.unit], c, k_of[c.unit]++));
-  }
+  plan->wave_items.reserve(wave_chunks.size());
+  for (const Chunk& c : wave_chunks) plan->wave_items.push_back(emit(wave_units[c.unit], c));
+  plan->group_items.reserve(group_chunks.size());
+  for (const Chunk& c : group_chunks) plan->group_items.push_back(emit(group_units[c.unit], c));
   return {};
 }
 
