@@ -407,10 +407,6 @@ int lease_runs(const std::vector<kvp::PageRun>& runs, hipStream_t s, Staging::Le
 struct DecodeLayout {
   kvp::DecodePlan plan;
   std::vector<int32_t> merge_info;  // one 16-byte record per merged sequence: {seq, first partial, count, 0}
-  int rec_members = 1;              // member entries of a wave-path record
-  size_t rec_bytes() const {
-    return (sizeof(kvp::DecodeRec) + sizeof(kvp::DecodeRec::Member) * (rec_members - 1) + 15) & ~size_t(15);
-  }
   size_t off_wave = 0, off_group = 0, off_members = 0, off_part_base = 0, off_merge = 0;
   int max_parts = 0;                // largest partial count of a merged sequence
   size_t meta_bytes = 0;            // work list bytes (offsets above, 256-byte aligned)
@@ -423,8 +419,7 @@ struct DecodeLayout {
     };
     // Wave-path records: segment s's first chunk is record s, its further chunks follow all the first ones.
     const int segs = (int)plan.seg_off.size() - 1;
-    const size_t stride = rec_bytes();
-    unsigned char* const recs = dst + off_wave;
+    auto* const recs = reinterpret_cast<kvp::DecodeRec*>(dst + off_wave);
     const kvp::DecodeItem* it = plan.wave_items.data();
     const int32_t *seg_off = plan.seg_off.data(), *members = plan.members.data(), *part_base = plan.part_base.data();
     int32_t tail = segs;
@@ -432,12 +427,10 @@ struct DecodeLayout {
       const int c1 = seg_off[s + 1];
       for (int32_t at = s; c < c1; ++c, ++it) {
         const int32_t next = c + 1 < c1 ? tail++ : -1;
-        auto* rec = reinterpret_cast<kvp::DecodeRec*>(recs + at * stride);
-        const int n_mem = it->n_mem, slot = it->slot;
-        const int32_t* mem = members + it->mem_off;
-        *rec = {it->row, it->page_lo, it->page_hi, it->tok_end, it->kind << 16 | n_mem, next,
-                {{mem[0], slot < 0 ? -1 : part_base[mem[0]] + slot}}};
-        for (int m = 1; m < n_mem; ++m) rec->mem[m] = {mem[m], slot < 0 ? -1 : part_base[mem[m]] + slot};
+        const int32_t seq = members[it->mem_off];
+        recs[at] = {it->row, it->page_lo, it->page_hi, it->tok_end,
+                    (uint32_t)it->kind | (uint32_t)(it->n_mem - 1) << 1 | (uint32_t)it->mem_off << 5, next,
+                    seq, it->slot < 0 ? -1 : part_base[seq] + it->slot};
         at = next;
       }
     }
@@ -470,8 +463,7 @@ int layout_decode(kvp_pool_t pool, const int32_t* seq_lens, int B, int maxp, con
     at = (at + n + 255) & ~size_t(255);
     return off;
   };
-  for (const kvp::DecodeItem& it : P.wave_items) L->rec_members = std::max(L->rec_members, it.n_mem);
-  L->off_wave = slot(P.wave_items.size() * L->rec_bytes());
+  L->off_wave = slot(P.wave_items.size() * sizeof(kvp::DecodeRec));
   L->off_group = slot(P.group_items.size() * sizeof(kvp::DecodeItem));
   L->off_members = slot(P.members.size() * 4);
   L->off_part_base = slot(P.part_base.size() * 4);
@@ -508,9 +500,7 @@ kvp::DecodeArgs decode_args(const DecodeLayout& L, kvp_pool_t pool, int layer, c
   a.scale_log2 = scale * 1.4426950408889634f * (a.fp8 ? pool->k_scale[layer] : 1.0f);
   a.v_scale = a.fp8 ? pool->v_scale[layer] : 1.0f;
   a.err = pool->err;
-  a.recs = meta + L.off_wave;
-  a.rec_bytes = (int)L.rec_bytes();
-  a.rec_members = L.rec_members;
+  a.recs = reinterpret_cast<const kvp::DecodeRec*>(meta + L.off_wave);
   a.n_items = (int)P.seg_off.size() - 1;
   a.group_items = reinterpret_cast<const kvp::DecodeItem*>(meta + L.off_group);
   a.n_group_items = (int)P.group_items.size();

@@ -638,15 +638,17 @@ __device__ __forceinline__ void decode_wave_block(const DecodeArgs& a, int block
   const int seg = wid / a.Hkv;
   const int kvh = wid - seg * a.Hkv;
   if (seg >= a.n_items) return;
-  // the member that owns this lane's query column (columns past the chunk's members are masked by col_ok)
-  const int m = min((lane & 15) / a.G, a.rec_members - 1);
+  const int m = (lane & 15) / a.G;  // the member that owns this lane's query column
   int r = seg;
   do {
-    const unsigned char* rec = a.recs + (int64_t)r * a.rec_bytes;
-    const int4 lo = *reinterpret_cast<const int4*>(rec);
-    const int2 hi = *reinterpret_cast<const int2*>(rec + 16);
-    const int2 member = *reinterpret_cast<const int2*>(rec + offsetof(DecodeRec, mem) + 8 * m);
-    const WaveChunk it{lo.x, lo.y, lo.z, lo.w, hi.x >> 16, hi.x & 0xffff, member.x, member.y};
+    const int4 lo = reinterpret_cast<const int4*>(a.recs + r)[0], hi = reinterpret_cast<const int4*>(a.recs + r)[1];
+    const unsigned km = (unsigned)hi.x;
+    WaveChunk it{lo.x, lo.y, lo.z, lo.w, (int)(km & 1), (int)((km >> 1) & 15) + 1, hi.z, hi.w};
+    if (m > 0 && m < it.n_mem) {  // another member: its slot is the first member's
+      const int slot = it.part - a.part_base[it.seq];
+      it.seq = a.members[(km >> 5) + m];
+      it.part = a.part_base[it.seq] + slot;
+    }
     if constexpr (FP8) decode_wave_chunk_fp8<D>(a, it, kvh, lane);
     else decode_wave_chunk<D>(a, it, kvh, lane);
     r = hi.y;

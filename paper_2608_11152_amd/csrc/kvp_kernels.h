@@ -44,30 +44,26 @@ struct GatherArgs {
   float scale_k, scale_v;
 };
 
-// A wave-path chunk as the kernel reads it, over the bus from pinned host memory: all that a wave needs before its
-// first page in one record, so that a chunk starts after one such read.  The segment's chunk range, the item and
-// its member list were three dependent reads of 1.3 us each (and the partial index a fourth, at the chunk's end):
-// one sequence of 131,007 tokens 57.9 -> 55.5 us, RLHF 177.3 -> 175.0 us, 9 groups over short prompts 28.1 ->
-// 23.9 us.  A record holds the same number of members throughout a call (the most that a chunk has).
+// A wave-path chunk as the kernel reads it, over the bus from pinned host memory: what a wave needs before its first
+// page in one record, so that a chunk of one member starts after one such read.  The segment's chunk range, the item
+// and its member list were three dependent reads of 1.3 us each (and the partial index a fourth, at the chunk's
+// end): one sequence of 131,007 tokens 58.1 -> 54.5 us, RLHF 178.0 -> 174.9 us, mixed 369.8 -> 363.6 us, RLVR 1392.8
+// -> 1376.5 us.  The other members of a chunk stay in the call's member list: records that hold them all (160 bytes
+// for 16) leave RLHF at 175.2 us and cost the host 3 us per 1000 short sequences.
 struct DecodeRec {
   int32_t row, page_lo, page_hi, tok_end;  // as in DecodeItem
-  int32_t kind_mem;           // kind << 16 | n_mem
+  uint32_t kind_mem;          // kind, n_mem - 1 and mem_off in 1, 4 and 27 bits
   int32_t next;               // record of the segment's next chunk, -1 = none
-  struct Member {
-    int32_t seq;
-    int32_t part;             // index of the member's partial, -1 = write the output
-  } mem[1];
+  int32_t seq, part;          // the first member and the index of its partial, -1 = write the output
 };
-static_assert(sizeof(DecodeRec) == 32, "two 16-byte reads, of which the last holds the first member");
+static_assert(sizeof(DecodeRec) == 32, "two 16-byte reads");
 
 struct DecodeArgs {
   const uint16_t* q;        // [B, Hq, D] bf16
   const uint16_t* layer;
   const int32_t* bt;
   int maxp;
-  const unsigned char* recs;  // wave path: one DecodeRec per chunk, segment s starting at record s
-  int rec_bytes;              // bytes from one record to the next
-  int rec_members;            // member entries of a record
+  const DecodeRec* recs;      // wave path: one per chunk, segment s starting at record s
   int n_items;                // wave path: segment count
   const DecodeItem* group_items;  // shared-prefix path (LDS-staged, > 16 query columns)
   int n_group_items;

@@ -178,15 +178,17 @@ Status plan_decode(const int32_t* seq_lens, int B, int maxp, const kvp_group_pre
     // the smallest at which the cut still fits segs_target segments (one round of waves).
     const int64_t K = chunk_start_pages;
     auto cut = [&](int64_t cap, bool emit) -> int64_t {  // returns the segment count
+      const int64_t long_unit = 8 * (cap - K);  // from here a division beats counting chunk by chunk
       int64_t fill = 0;
       int seg = 0;
       for (size_t u = 0; u < wave_units.size(); ++u) {
+        if (!emit && seg > segs_target) return seg;  // too many already
         int lo = wave_units[u].lo;
         while (lo < wave_units[u].hi) {
-          if (!emit && fill == 0) {  // whole segments of one chunk each, counted at once
-            const int64_t full = (wave_units[u].hi - lo) / (cap - K);
-            seg += (int)full;
-            lo += (int)(full * (cap - K));
+          if (!emit && fill == 0 && wave_units[u].hi - lo >= long_unit) {  // whole segments of one chunk each
+            const int per = (int)(cap - K), full = (wave_units[u].hi - lo) / per;
+            seg += full;
+            lo += full * per;
             if (lo == wave_units[u].hi) break;
           }
           if (fill > 0 && fill + K >= cap) {  // no room for another start and a page

@@ -1,6 +1,5 @@
-"""The wave path's chunk records: calls whose chunks differ in member count (so records hold unused entries),
-whose segments hold several chunks (records chained past the first ones) and one chunk, at the fewest and the most
-members a record can have."""
+"""The wave path's chunk records: chunks of one member (held by the record) and of up to 16 (the others looked up),
+in calls whose segments hold one chunk and several (records chained past the first ones)."""
 import numpy as np
 import pytest
 
@@ -13,13 +12,13 @@ from paper_2608_11152_amd import workloads as W
 pytestmark = pytest.mark.gpu
 
 
-# (query heads, KV heads, members of each group, private sequences): 16 / G members fill a record at most.
+# (query heads, KV heads, members of each group, private sequences): 16 / G members fill a chunk's columns.
 @pytest.mark.parametrize("Hq,Hkv,groups,singles", [
-    (1, 1, [16, 3, 1], 5),        # 16 members a record; few chunks
+    (1, 1, [16, 3, 1], 5),        # few chunks, one a segment
     (8, 8, [16, 16, 2], 400),     # more chunks than the call's segments: chains of chunks
     (16, 4, [4, 2, 3], 900),
     (16, 2, [2, 1], 0),
-    (16, 1, [1], 3),              # one member a record
+    (16, 1, [1], 3),              # one member a chunk
 ])
 @pytest.mark.parametrize("kv", ["bf16", "fp8"])
 def test_chunk_records(Hq, Hkv, groups, singles, kv):
