@@ -554,13 +554,20 @@ int check_decode_args(kvp_pool_t pool, int layer, const void* q, const int32_t* 
   return KVP_OK;
 }
 
-// Prefill: the caller's workspace holds the metadata (work list, lengths, split bookkeeping, one async
-// copy) followed by the partial states of split tiles [partial accumulators][partial (m, l)].
+// Prefill: the caller's workspace holds [metadata: work list, merge records][partial accumulators][partial (m, l)].
+// A short work list without merge records is read where decode's is, from its pinned staging piece, and its part
+// of the workspace stays unused: the copy kernel and its launch were 3 us of a 17 us call (1 session of 16 tokens
+// 17.0 -> 14.2 us, 32 of 100 tokens, 512 items, 24.4 -> 22.9).  Past kPrefillPinnedItems the 48-byte reads over
+// the bus, one per workgroup, cost more than the copy (64 of 100 tokens, 1024 items, 39.4 -> 40.0 us; 64 of 128 to
+// 1024 tokens 363.4 -> 367.1), and so do merge records, read by every merge workgroup (16 of 64 tokens over 2000
+// cached 57.1 -> 58.5).
+constexpr int kPrefillPinnedItems = 512;
 struct PrefillLayout {
   kvp::PrefillPlan plan;
   Packer meta;
   size_t off_items = 0, off_merge = 0;
   int max_parts = 0;  // largest range count of a merged query row
+  bool read_pinned = false;
   size_t off_acc = 0, off_ml = 0, total = 0;
 };
 
@@ -573,23 +580,24 @@ int layout_prefill(kvp_pool_t pool, const int32_t* ctx_lens, const int32_t* cu_q
   const std::vector<kvp::PrefillWork> work = kvp::prefill_work(P, ctx_lens, cu_q, Hq / pool->num_kv_heads);
   L->off_items = L->meta.add(work.data(), work.size() * sizeof(kvp::PrefillWork));
   L->off_merge = L->meta.add(P.merge_info.data(), P.merge_info.size() * 4);
+  L->read_pinned = P.merge_info.empty() && (int)P.items.size() <= kPrefillPinnedItems;
   L->off_acc = L->meta.size();
   L->off_ml = L->off_acc + (((size_t)P.total_parts * Hq * pool->head_dim * 4 + 255) & ~size_t(255));
   L->total = L->off_ml + (((size_t)P.total_parts * Hq * 8 + 255) & ~size_t(255));
   return KVP_OK;
 }
 
-// Kernel arguments of a laid-out prefill plan whose metadata and partial states sit in the device
-// workspace `w` (metadata uploaded there first).
+// Kernel arguments of a laid-out prefill plan whose partial states go to the device
+// workspace `w`; the metadata sits at `meta` (stage_prefill).
 kvp::PrefillArgs prefill_args(const PrefillLayout& L, kvp_pool_t pool, int layer, const void* q,
                               const int32_t* block_tables, int maxp, int num_q_heads, float scale, void* out,
-                              int out_dtype, unsigned char* w) {
+                              int out_dtype, const unsigned char* meta, unsigned char* w) {
   kvp::PrefillArgs a{};
   a.q = reinterpret_cast<const uint16_t*>(q);
   a.layer = layer_ptr(pool, layer);
   a.bt = block_tables;
   a.maxp = maxp;
-  a.items = reinterpret_cast<const kvp::PrefillWork*>(w + L.off_items);
+  a.items = reinterpret_cast<const kvp::PrefillWork*>(meta + L.off_items);
   a.n_items = (int)L.plan.items.size();
   const int64_t stages = kvp::prefill_mean_stages(L.plan);
   a.long_items = pool->dtype == KVP_BF16 && pool->head_dim == 128 && stages >= kvp::kPrefillLongStages;
@@ -608,6 +616,19 @@ kvp::PrefillArgs prefill_args(const PrefillLayout& L, kvp_pool_t pool, int layer
   a.v_scale = a.fp8 ? pool->v_scale[layer] : 1.0f;
   a.err = pool->err;
   return a;
+}
+
+// Puts the metadata of a prefill plan where its kernels read it: `*meta` is a pinned staging piece (the caller
+// releases `lease` behind the last kernel that reads it), or the workspace, after a copy.
+int stage_prefill(const PrefillLayout& L, unsigned char* w, hipStream_t s, Staging::Lease* lease,
+                  const unsigned char** meta) {
+  *meta = w;
+  if (!L.read_pinned) return staging().upload(w, L.meta.buf.data(), L.meta.buf.size(), s);
+  const int rc = staging().lease(L.meta.buf.size(), s, lease);
+  if (rc) return rc;
+  std::memcpy(lease->host, L.meta.buf.data(), L.meta.buf.size());
+  *meta = reinterpret_cast<const unsigned char*>(lease->host);
+  return KVP_OK;
 }
 
 // Checks of the prefill entry points (before anything is planned or enqueued).
@@ -1239,15 +1260,20 @@ int prefix_chunk_prefill_attn(const void* q, kvp_pool_t pool, int layer, const i
     return set_err(KVP_EWORKSPACE, "workspace of %zu bytes, %zu needed", ws ? ws_bytes : (size_t)0, L.total);
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   unsigned char* w = reinterpret_cast<unsigned char*>(ws);
-  rc = staging().upload(w, L.meta.buf.data(), L.meta.buf.size(), s);
+  Staging::Lease lease;
+  const unsigned char* meta = nullptr;
+  rc = stage_prefill(L, w, s, &lease, &meta);
   if (rc) return rc;
-  const kvp::PrefillArgs a = prefill_args(L, pool, layer, q, block_tables, maxp, num_q_heads, scale, out, out_dtype, w);
+  const kvp::PrefillArgs a =
+      prefill_args(L, pool, layer, q, block_tables, maxp, num_q_heads, scale, out, out_dtype, meta, w);
   hipError_t e = kvp::launch_prefill(a, pool->head_dim, s);
   // split tiles: combine each query row's key ranges (the decode merge, one record per query row)
   if (e == hipSuccess)
-    e = launch_merge(reinterpret_cast<const int32_t*>(w + L.off_merge), (int)(L.plan.merge_info.size() / 4),
+    e = launch_merge(reinterpret_cast<const int32_t*>(meta + L.off_merge), (int)(L.plan.merge_info.size() / 4),
                      L.max_parts, a.part_acc, a.part_ml, out, a.out_f32, num_q_heads, pool, s);
-  return e == hipSuccess ? KVP_OK : hip_err(e, "prefix_chunk_prefill_attn launch");
+  const int rr = lease.slot >= 0 ? staging().release(lease) : KVP_OK;
+  if (e != hipSuccess) return hip_err(e, "prefix_chunk_prefill_attn launch");
+  return rr;
 }
 
 int mixed_step_workspace_size(kvp_pool_t pool, const int32_t* seq_lens, int num_dec, const kvp_group_prefix* group_prefix,
@@ -1282,7 +1308,8 @@ int mixed_step_attn(kvp_pool_t pool, int layer, int num_q_heads, float scale, in
   unsigned char* w = reinterpret_cast<unsigned char*>(ws);
   kvp::DecodeArgs d{};
   kvp::PrefillArgs p{};
-  Staging::Lease lease;
+  Staging::Lease lease, lease_pf;
+  const unsigned char* meta_pf = nullptr;
   if (num_dec > 0) {
     // the decode work list is read from a pinned staging slot, as in paged_decode_attn
     rc = staging().lease(L.dec.meta_bytes, s, &lease);
@@ -1293,26 +1320,28 @@ int mixed_step_attn(kvp_pool_t pool, int layer, int num_q_heads, float scale, in
   }
   hipError_t e = hipSuccess;
   if (has_pf) {
-    rc = staging().upload(w + L.off_pf, L.pf.meta.buf.data(), L.pf.meta.buf.size(), s);
+    rc = stage_prefill(L.pf, w + L.off_pf, s, &lease_pf, &meta_pf);
     if (rc) {
       if (num_dec > 0) (void)staging().release(lease);
       return rc;
     }
     p = prefill_args(L.pf, pool, layer, q_pf, block_tables_pf, maxp_pf, num_q_heads, scale, out_pf, out_dtype,
-                     w + L.off_pf);
+                     meta_pf, w + L.off_pf);
   }
   if (num_dec > 0) e = kvp::launch_decode(d, pool->head_dim, s);
   if (e == hipSuccess && has_pf) e = kvp::launch_prefill(p, pool->head_dim, s);
   if (e == hipSuccess && num_dec > 0)
     e = launch_merge(reinterpret_cast<const int32_t*>(reinterpret_cast<const unsigned char*>(lease.host) +
                                                       L.dec.off_merge),
-                     (int)L.dec.plan.merge_seqs.size(), L.dec.max_parts, d.part_acc, d.part_ml, out_dec, d.out_f32, num_q_heads,
-                     pool, s);
+                     (int)L.dec.plan.merge_seqs.size(), L.dec.max_parts, d.part_acc, d.part_ml, out_dec, d.out_f32,
+                     num_q_heads, pool, s);
   if (e == hipSuccess && has_pf)
-    e = launch_merge(reinterpret_cast<const int32_t*>(w + L.off_pf + L.pf.off_merge),
-                     (int)(L.pf.plan.merge_info.size() / 4), L.pf.max_parts, p.part_acc, p.part_ml, out_pf, p.out_f32, num_q_heads,
-                     pool, s);
-  const int rr = num_dec > 0 ? staging().release(lease) : KVP_OK;
+    e = launch_merge(reinterpret_cast<const int32_t*>(meta_pf + L.pf.off_merge),
+                     (int)(L.pf.plan.merge_info.size() / 4), L.pf.max_parts, p.part_acc, p.part_ml, out_pf, p.out_f32,
+                     num_q_heads, pool, s);
+  int rr = num_dec > 0 ? staging().release(lease) : KVP_OK;
+  const int rp = lease_pf.slot >= 0 ? staging().release(lease_pf) : KVP_OK;
+  if (rr == KVP_OK) rr = rp;
   if (e != hipSuccess) return hip_err(e, "mixed_step_attn launch");
   return rr;
 }
