@@ -4,9 +4,9 @@
 // Calls with short key ranges, FP8 pages or d = 64 (the others: prefill_long.hip).  One workgroup of W waves
 // per (session, KV head, 32 W flattened query rows, key range): W = 8 takes an item, a tile of 256 rows, whole;
 // W = 4 gives each half of it a workgroup of its own, two to a CU.  Query rows are flattened as
-// position * G + head-in-group, so every K/V tile loaded serves all G query heads of its KV head.  Keys stream through LDS in stages of 4 pages (64 keys), double-buffered: the next stage is loaded into
-// registers while this stage's MFMA work runs, then stored to the other buffer.  Wave w owns 32 query
-// rows:
+// position * G + head-in-group, so every K/V tile loaded serves all G query heads of its KV head.  Keys stream
+// through LDS in stages of 4 pages (64 keys), double-buffered: the next stage is loaded into registers while this
+// stage's MFMA work runs, then stored to the other buffer.  Wave w owns 32 query rows:
 //   S^T (64 keys x 32 rows) = K Q^T      v_mfma_f32_32x32x16_bf16, 2 key tiles x D/16 k-steps
 //   O^T (D x 32 rows)      += V^T P^T    the score tile's registers are the P^T operand (per page)
 // Masking is applied only to stages that reach past the wave's first query position (the diagonal).

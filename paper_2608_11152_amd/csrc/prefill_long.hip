@@ -18,8 +18,8 @@
 //    MFMA by MFMA, so no part waits for another of its step.  Scheduling barriers keep the order.
 //  * Pages go from the pool straight to LDS, two stages ahead in a ring of four (through registers: 16.8 ms).
 // Measured (MI355X): eight 2048-token chunks over 32k-131k histories 17.9 -> 16.3 ms (1.14 -> 1.25 PFLOP/s),
-// a 64-token chunk over 131k 157 -> 147 us; the start costs about 10 us more per workgroup (queries for 64 rows per wave,
-// the first and last half not interleaved), hence the rule in kvp_plan.h.
+// a 64-token chunk over 131k 157 -> 147 us; the start costs about 10 us more per workgroup (queries for 64 rows
+// per wave, the first and last half not interleaved), hence the rule in kvp_plan.h.
 #include <type_traits>
 #include <utility>
 
@@ -119,9 +119,10 @@ __global__ __launch_bounds__(256, 1) void prefill_long_kernel(PrefillArgs a) {
   // Piece K of a page straight to LDS (the immediate offset moves both sides; it holds 4 KB).
   auto dma_piece = [&](auto K, unsigned char* dst, const unsigned char* src, uint32_t off) {
     constexpr int k = decltype(K)::value;
-    const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(src), 0, PB, 0x00020000);
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)(dst + (k / 4) * 4096), 16, off,
-                                             (k / 4) * 4096, (k % 4) * 1024, 0);
+    const __amdgpu_buffer_rsrc_t r =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(src), 0, PB, 0x00020000);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)(dst + (k / 4) * 4096), 16,
+                                             off, (k / 4) * 4096, (k % 4) * 1024, 0);
   };
   // The first two stages' page ids, the queries, the two stages: the waits are in the order of the loads.
   u32x4 qt[NC][NS];
