@@ -55,7 +55,7 @@ def parse():
     ap.add_argument("--no-flush", action="store_true", help="do not evict the Infinity Cache between steps")
     ap.add_argument("--no-fp8", action="store_true", help="skip the FP8-KV leg (same step over an FP8 pool)")
     ap.add_argument("--no-mixed-step", action="store_true",
-                    help="skip the leg that times the step's attention as one mixed_step_attn launch")
+                    help="skip the leg that times the step's attention as one mixed_step_attn call")
     ap.add_argument("--no-prefill-split", action="store_true",
                     help="skip the split-history prefill leg (keeps a profile's prefill and merge kernels to the step)")
     return ap.parse_args()
@@ -329,7 +329,7 @@ def prefill_split_leg(kp, dev, stream, ctx: int = 131072, chunks=(64, 256), reps
 
 def mixed_step_leg(kp, pool, w, vals, gp, bt, flush, stream, s0: int, s1: int, cu_q, reps: int = 10) -> dict:
     """The step's attention (decode of every sequence and prefill of the chunks) as one mixed_step_attn
-    launch, against the two separate calls, on the same pool and inputs: runs interleaved, each after the
+    call, against the two separate calls, on the same pool and inputs: runs interleaved, each after the
     cache flush, timed with HIP events on the launch stream.  The outputs are compared bitwise."""
     import torch
     dev = vals.q.device
