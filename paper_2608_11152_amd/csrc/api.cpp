@@ -14,6 +14,7 @@
 #include <vector>
 
 #include "kvp_kernels.h"
+#include "staging.h"
 
 struct kvp_prefix_table {
   uint64_t* keys = nullptr;
@@ -65,178 +66,45 @@ int hip_err(hipError_t e, const char* what) {
   return set_err(KVP_EHIP, "%s: %s", what, hipGetErrorString(e));
 }
 
-// Pinned host memory for the work lists of calls.  A call leases a piece, the GPU reads it (copied into
-// device memory by `upload`: a small copy kernel on the caller's stream, not the copy engine, whose hand-off
-// to the compute queue measured 20-30 us per call; or, for metadata each wave reads once, read by the kernels
-// directly over the bus: `lease` ... `release`), and the piece is written again only after that work.
-//
-// Pieces are cut from blocks, each open for one stream; a block that has no room for the next piece is closed
-// by recording one event behind its work, and is used again once the event has completed.  An event behind
-// every call costs the stream a 5.6 us gap before its next kernel (kernel trace; no gap between kernels
-// without one): mixed decode 371.8 -> 369.1 us, RLHF 180.2 -> 177.2 us, a 67 MB append 20.7 -> 17.2 us
-// without.  Blocks open for a stream that has gone quiet are not reused (nothing was recorded behind their
-// work), so at most kMaxOpen of them stay open: past that every release closes its block.
-class Staging {
- public:
-  struct Lease {
-    void* host = nullptr;
-    int slot = -1;
-  };
-
-  int lease(size_t n, hipStream_t s, Lease* out) {
-    int dev = 0;
-    hipError_t e = hipGetDevice(&dev);
-    if (e != hipSuccess) return hip_err(e, "hipGetDevice");
-    n = (n + 255) & ~size_t(255);
-    std::lock_guard<std::mutex> lock(mu_);
-    int idx = -1;
-    for (int k = 0; k < kBlocks && idx < 0; ++k) {
-      Block& b = blocks_[k];
-      if (b.state != kOpen || b.stream != s || b.device != dev || b.closing) continue;
-      if (b.used + n <= b.cap) {
-        idx = k;
-      } else {
-        const int rc = close(&b);
-        if (rc) return rc;
-      }
-    }
-    if (idx < 0) {
-      const int rc = acquire(n, dev, &idx);
-      if (rc) return rc;
-      Block& b = blocks_[idx];
-      b.state = kOpen;
-      b.stream = s;
-      b.used = 0;
-      b.leases = 0;
-      // hipStreamPerThread names another stream in every thread: a block of its own, closed by this call
-      b.closing = s == hipStreamPerThread;
-    }
-    Block& b = blocks_[idx];
-    out->host = b.host + b.used;
-    out->slot = idx;
-    b.used += n;
-    b.leases++;
-    return KVP_OK;
+struct HipRt {
+  using Stream = hipStream_t;
+  using Event = hipEvent_t;
+  static hipError_t get_device(int* dev) { return hipGetDevice(dev); }
+  static hipError_t event_create(hipEvent_t* ev) { return hipEventCreateWithFlags(ev, hipEventDisableTiming); }
+  static void event_destroy(hipEvent_t ev) { (void)hipEventDestroy(ev); }
+  static hipError_t event_record(hipEvent_t ev, hipStream_t s) { return hipEventRecord(ev, s); }
+  static hipError_t event_wait(hipEvent_t ev) { return hipEventSynchronize(ev); }
+  static bool event_done(hipEvent_t ev) {
+    if (hipEventQuery(ev) == hipSuccess) return true;
+    (void)hipGetLastError();  // hipErrorNotReady is no error
+    return false;
   }
-
-  // Marks the end of the call that leased the piece: the GPU work that reads it is enqueued on the stream
-  // given to `lease` (or, after a failed launch, none is).
-  int release(const Lease& l) {
-    std::lock_guard<std::mutex> lock(mu_);
-    Block& b = blocks_[l.slot];
-    b.leases--;
-    if (b.leases > 0) return KVP_OK;
-    int open = 0;
-    for (const Block& x : blocks_) open += x.state == kOpen;
-    return b.closing || open > kMaxOpen ? close(&b) : KVP_OK;
-  }
-
-  int upload(void* dst, const void* src, size_t n, hipStream_t s) {
-    if (n == 0) return KVP_OK;
-    Lease l;
-    int rc = lease(n, s, &l);
-    if (rc) return rc;
-    std::memcpy(l.host, src, n);
-    hipError_t e = kvp::launch_copy_from_host(dst, l.host, n, s);
-    rc = release(l);
-    return e != hipSuccess ? hip_err(e, "metadata copy") : rc;
-  }
-
- private:
-  static constexpr int kBlocks = 12;
-  static constexpr int kMaxOpen = 4;
-  static constexpr size_t kBlockBytes = 1 << 20;
-  enum State { kFree, kOpen, kPending };
-  struct Block {
-    unsigned char* host = nullptr;
-    size_t cap = 0, used = 0;
-    State state = kFree;
-    hipStream_t stream = nullptr;
-    int device = -1;        // device of the event
-    int leases = 0;         // calls between lease and release
-    bool closing = false;   // full: the last release records the event
-    hipEvent_t ev = nullptr;
-    uint64_t closed = 0;    // order of closing
-  };
-
-  // Record the event behind the block's work (by the last release if calls still hold pieces).
-  int close(Block* b) {
-    if (b->leases > 0) {
-      b->closing = true;
-      return KVP_OK;
-    }
-    b->closing = false;
-    const hipError_t e = hipEventRecord(b->ev, b->stream);
-    if (e != hipSuccess) return hip_err(e, "hipEventRecord");
-    b->state = kPending;
-    b->closed = ++order_;
-    return KVP_OK;
-  }
-
-  // A block of at least n bytes that nothing reads, with an event of device `dev`.
-  int acquire(size_t n, int dev, int* out) {
-    int best = -1;
-    auto oldest = [&]() {
-      int k0 = -1;
-      for (int k = 0; k < kBlocks; ++k)
-        if (blocks_[k].state == kPending && (k0 < 0 || blocks_[k].closed < blocks_[k0].closed)) k0 = k;
-      return k0;
-    };
-    for (int k = oldest(); k >= 0; k = oldest()) {  // blocks whose work has completed
-      if (hipEventQuery(blocks_[k].ev) != hipSuccess) {
-        (void)hipGetLastError();  // hipErrorNotReady is no error
-        break;
-      }
-      blocks_[k].state = kFree;
-    }
-    for (int k = 0; k < kBlocks; ++k)
-      if (blocks_[k].state == kFree && (best < 0 || rank(blocks_[k], n, dev) < rank(blocks_[best], n, dev))) best = k;
-    if (best < 0 && (best = oldest()) >= 0) {
-      const hipError_t e = hipEventSynchronize(blocks_[best].ev);
-      if (e != hipSuccess) return hip_err(e, "hipEventSynchronize(staging)");
-      blocks_[best].state = kFree;
-    }
-    if (best < 0) return set_err(KVP_EINVAL, "more than %d concurrent calls hold metadata slots", kBlocks);
-    Block& b = blocks_[best];
-    if (b.ev && b.device != dev) {
-      (void)hipEventDestroy(b.ev);
-      b.ev = nullptr;
-    }
-    if (!b.ev) {
-      const hipError_t e = hipEventCreateWithFlags(&b.ev, hipEventDisableTiming);
-      if (e != hipSuccess) return hip_err(e, "hipEventCreate");
-      b.device = dev;
-    }
-    if (n > b.cap) {
-      if (b.host) (void)hipHostFree(b.host);
-      b.host = nullptr;
-      b.cap = 0;
-      const size_t cap = std::max(n, kBlockBytes);
-      const hipError_t e = hipHostMalloc(reinterpret_cast<void**>(&b.host), cap, hipHostMallocDefault);
-      if (e != hipSuccess) {
-        b.host = nullptr;
-        return set_err(KVP_ENOMEM, "hipHostMalloc(%zu): %s", cap, hipGetErrorString(e));
-      }
-      b.cap = cap;
-    }
-    *out = best;
-    return KVP_OK;
-  }
-
-  // Which free block to take: one that fits on the same device, then one to allocate, then one to replace.
-  static int rank(const Block& b, size_t n, int dev) {
-    if (b.cap >= n) return b.device == dev ? 0 : 1;
-    return b.cap == 0 ? 2 : 3;
-  }
-
-  std::mutex mu_;
-  Block blocks_[kBlocks];
-  uint64_t order_ = 0;
+  static hipError_t host_alloc(void** p, size_t n) { return hipHostMalloc(p, n, hipHostMallocDefault); }
+  static void host_free(void* p) { (void)hipHostFree(p); }
+  static const char* error_string(hipError_t e) { return hipGetErrorString(e); }
+  static int hip_fail(hipError_t e, const char* what) { return hip_err(e, what); }
+  template <class... A>
+  static int fail(int code, const char* fmt, A... a) { return set_err(code, fmt, a...); }
 };
+
+using Staging = kvp::StagingOf<HipRt>;
 
 Staging& staging() {
   static Staging* s = new Staging();  // intentionally leaked: outlives static destruction order
   return *s;
+}
+
+// Copies n bytes of host memory to device memory through a staging piece: a small copy kernel on the stream, not
+// the copy engine, whose hand-off to the compute queue measured 20-30 us per call.
+int upload(void* dst, const void* src, size_t n, hipStream_t s) {
+  if (n == 0) return KVP_OK;
+  Staging::Lease l;
+  int rc = staging().lease(n, s, &l);
+  if (rc) return rc;
+  std::memcpy(l.host, src, n);
+  const hipError_t e = kvp::launch_copy_from_host(dst, l.host, n, s);
+  rc = staging().release(l, e == hipSuccess);
+  return e != hipSuccess ? hip_err(e, "metadata copy") : rc;
 }
 
 // Device address of `scratch` on device `dev` (the current device), looked up once per device.
@@ -387,7 +255,7 @@ int run_tier(kvp_pool_t pool, int layer, const std::vector<kvp::TierItem>& items
   a.bt = bt;
   a.maxp = maxp;
   hipError_t e = kvp::launch_tier(a, restore, s);
-  const int rr = staging().release(lease);
+  const int rr = staging().release(lease, e == hipSuccess);
   if (e != hipSuccess) return hip_err(e, restore ? "kv_restore launch" : "kv_offload launch");
   return rr;
 }
@@ -623,7 +491,7 @@ kvp::PrefillArgs prefill_args(const PrefillLayout& L, kvp_pool_t pool, int layer
 int stage_prefill(const PrefillLayout& L, unsigned char* w, hipStream_t s, Staging::Lease* lease,
                   const unsigned char** meta) {
   *meta = w;
-  if (!L.read_pinned) return staging().upload(w, L.meta.buf.data(), L.meta.buf.size(), s);
+  if (!L.read_pinned) return upload(w, L.meta.buf.data(), L.meta.buf.size(), s);
   const int rc = staging().lease(L.meta.buf.size(), s, lease);
   if (rc) return rc;
   std::memcpy(lease->host, L.meta.buf.data(), L.meta.buf.size());
@@ -849,7 +717,7 @@ int kv_append(kvp_pool_t pool, int layer, const void* k, const void* v, const in
   a.inv_scale_k = 1.0f / pool->k_scale[layer];
   a.inv_scale_v = 1.0f / pool->v_scale[layer];
   hipError_t e = kvp::launch_append(a, pool->head_dim, s);
-  const int rr = staging().release(lease);
+  const int rr = staging().release(lease, e == hipSuccess);
   if (e != hipSuccess) return hip_err(e, "kv_append launch");
   return rr;
 }
@@ -893,7 +761,7 @@ int kv_gather(kvp_pool_t pool, int layer, const int32_t* block_tables, int maxp,
   a.scale_k = pool->k_scale[layer];
   a.scale_v = pool->v_scale[layer];
   hipError_t e = kvp::launch_gather(a, pool->head_dim, s);
-  const int rr = staging().release(lease);
+  const int rr = staging().release(lease, e == hipSuccess);
   if (e != hipSuccess) return hip_err(e, "kv_gather launch");
   return rr;
 }
@@ -983,7 +851,7 @@ int kvp_block_hashes(const int32_t* tokens, const int32_t* cu_tokens, int num_se
   a.seq_first = reinterpret_cast<const int32_t*>(host + nb);
   a.out = hashes;
   const hipError_t e = kvp::launch_block_hash(a, (int)chunks.size(), (int)seq_first.size(), s);
-  const int rr = staging().release(lease);
+  const int rr = staging().release(lease, e == hipSuccess);
   if (e != hipSuccess) return hip_err(e, "kvp_block_hashes launch");
   return rr;
 }
@@ -1016,7 +884,7 @@ int kvp_group_shared_pages(const uint64_t* hashes, const int32_t* cu_tokens, int
   int rc = lease_seq_info(cu_tokens, num_seqs, s, &lease, &pages, extra, &off);
   if (rc) return rc;
   if (pages > 0 && !hashes) {
-    (void)staging().release(lease);
+    (void)staging().release(lease, false);
     return set_err(KVP_EINVAL, "hashes is NULL");
   }
   const unsigned char* h = reinterpret_cast<const unsigned char*>(lease.host);
@@ -1027,7 +895,7 @@ int kvp_group_shared_pages(const uint64_t* hashes, const int32_t* cu_tokens, int
   a.members = reinterpret_cast<const int32_t*>(h + moff);
   a.shared_pages = shared_pages;
   hipError_t e = kvp::launch_group_lcp(a, num_groups, s);
-  const int rr = staging().release(lease);
+  const int rr = staging().release(lease, e == hipSuccess);
   if (e != hipSuccess) return hip_err(e, "kvp_group_shared_pages launch");
   return rr;
 }
@@ -1152,7 +1020,7 @@ int kvp_prefix_lookup(kvp_prefix_table_t t, const uint64_t* hashes, const int32_
   a.out_pages = page_ids;
   a.err = t->err;
   const hipError_t e = kvp::launch_table(a, 2, (int)chunks.size(), s);
-  const int rr = staging().release(lease);
+  const int rr = staging().release(lease, e == hipSuccess);
   if (e != hipSuccess) return hip_err(e, "kvp_prefix_lookup launch");
   return rr;
 }
@@ -1201,7 +1069,7 @@ int paged_decode_attn(const void* q, kvp_pool_t pool, int layer, const int32_t* 
   hipError_t e = launch_decode_plan(L, pool, layer, q, block_tables, maxp, num_q_heads, scale, out, out_dtype,
                                     reinterpret_cast<const unsigned char*>(lease.host),
                                     reinterpret_cast<unsigned char*>(ws), s);
-  const int rr = staging().release(lease);
+  const int rr = staging().release(lease, e == hipSuccess);
   if (e != hipSuccess) return hip_err(e, "paged_decode_attn launch");
   return rr;
 }
@@ -1271,7 +1139,7 @@ int prefix_chunk_prefill_attn(const void* q, kvp_pool_t pool, int layer, const i
   if (e == hipSuccess)
     e = launch_merge(reinterpret_cast<const int32_t*>(meta + L.off_merge), (int)(L.plan.merge_info.size() / 4),
                      L.max_parts, a.part_acc, a.part_ml, out, a.out_f32, num_q_heads, pool, s);
-  const int rr = lease.slot >= 0 ? staging().release(lease) : KVP_OK;
+  const int rr = lease.slot >= 0 ? staging().release(lease, e == hipSuccess) : KVP_OK;
   if (e != hipSuccess) return hip_err(e, "prefix_chunk_prefill_attn launch");
   return rr;
 }
@@ -1322,7 +1190,7 @@ int mixed_step_attn(kvp_pool_t pool, int layer, int num_q_heads, float scale, in
   if (has_pf) {
     rc = stage_prefill(L.pf, w + L.off_pf, s, &lease_pf, &meta_pf);
     if (rc) {
-      if (num_dec > 0) (void)staging().release(lease);
+      if (num_dec > 0) (void)staging().release(lease, false);
       return rc;
     }
     p = prefill_args(L.pf, pool, layer, q_pf, block_tables_pf, maxp_pf, num_q_heads, scale, out_pf, out_dtype,
@@ -1339,8 +1207,8 @@ int mixed_step_attn(kvp_pool_t pool, int layer, int num_q_heads, float scale, in
     e = launch_merge(reinterpret_cast<const int32_t*>(meta_pf + L.pf.off_merge),
                      (int)(L.pf.plan.merge_info.size() / 4), L.pf.max_parts, p.part_acc, p.part_ml, out_pf, p.out_f32,
                      num_q_heads, pool, s);
-  int rr = num_dec > 0 ? staging().release(lease) : KVP_OK;
-  const int rp = lease_pf.slot >= 0 ? staging().release(lease_pf) : KVP_OK;
+  int rr = num_dec > 0 ? staging().release(lease, e == hipSuccess) : KVP_OK;
+  const int rp = lease_pf.slot >= 0 ? staging().release(lease_pf, e == hipSuccess) : KVP_OK;
   if (rr == KVP_OK) rr = rp;
   if (e != hipSuccess) return hip_err(e, "mixed_step_attn launch");
   return rr;

@@ -1,5 +1,5 @@
 """Pinned metadata blocks turned over while the GPU is behind: a block is written again only after the work
-that read it, on one stream and on more streams than blocks stay open for."""
+that read it, on the null stream (many pieces to a block) and on other streams (a block per call)."""
 import numpy as np
 import pytest
 
@@ -9,35 +9,53 @@ from paper_2608_11152_amd import kvpattn as kp
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("n_streams,calls", [(1, 80), (6, 60)])
-def test_metadata_blocks_under_pending_work(n_streams, calls):
-    """Each call's page runs take about 190 KB of a 1 MB block: the calls go through every block and wait for
-    the first.  Call c writes every sequence's token at position c of its stream's pages; a block handed out
-    too early would give an earlier call a later one's positions."""
+@pytest.mark.parametrize("n_streams,calls,behind", [(0, 80, 55), (1, 40, 11), (6, 60, 11)])
+def test_metadata_blocks_under_pending_work(n_streams, calls, behind):
+    """Each call's page runs take about 190 KB of a 1 MB block (the last quarter's, over 1 MB, replace blocks): the
+    calls go through every one of the 12 blocks and wait for the first.  Call c writes every sequence's token at
+    position c of its stream's pages; a block handed out too early would give an earlier call a later one's
+    positions.  The GPU is still behind at call `behind`, before the first block must be used again."""
     import torch
-    B, maxp, Hkv, d = 8000, (calls + 15) // 16, 1, 64
-    streams = [torch.cuda.Stream() for _ in range(n_streams)]
-    pools = [kp.Pool(1, B * maxp, Hkv, d) for _ in streams]
-    bt = torch.randperm(B * maxp, device="cuda").to(torch.int32).view(B, maxp).contiguous()
-    x = torch.randn(calls, B, Hkv, d, device="cuda").to(torch.bfloat16)
+    B, big, Hkv, d = 8000, 48000, 1, 64
+    streams = [torch.cuda.Stream() for _ in range(n_streams)] or [torch.cuda.default_stream()]
+    n = len(streams)
+    maxp = (calls // n + 15) // 16
+    pools = [kp.Pool(1, big * maxp, Hkv, d) for _ in streams]
+    bt = torch.randperm(big * maxp, device="cuda").to(torch.int32).view(big, maxp).contiguous()
+    x = torch.randn(calls, big, Hkv, d, device="cuda").to(torch.bfloat16)
     busy = torch.randn(4096, 4096, device="cuda")
+    size = [B if c < calls - calls // 4 else big for c in range(calls)]
+    cu = np.arange(big + 1, dtype=np.int32)
+    scratch = kp.Pool(1, B, Hkv, d)
+    for s in streams:  # pins the blocks
+        for c in range(12 if n_streams else 60):
+            kp.kv_append(scratch, 0, x[0][:B], x[0][:B], bt[:B, :1].contiguous() % B, np.zeros(B, np.int32), cu[:B + 1],
+                         stream=s)
     torch.cuda.synchronize()
-    note(f"metadata blocks: {calls} appends on {n_streams} streams behind pending work")
+    note(f"metadata blocks: {calls} appends on {n_streams or 'the null'} stream(s) behind pending work")
+    done = []
     for s in streams:
         with torch.cuda.stream(s):
-            for _ in range(10):
+            for _ in range(60):
                 torch.mm(busy, busy)
-    cu = np.arange(B + 1, dtype=np.int32)
+            done.append(torch.cuda.Event())
+            done[-1].record(s)
     for c in range(calls):
-        k = c % n_streams
-        pos = np.full(B, c // n_streams, np.int32)
-        kp.kv_append(pools[k], 0, x[c], x[c], bt, pos, cu, stream=streams[k])
+        if c == behind:
+            assert not any(e.query() for e in done), "the GPU is not behind: the test shows nothing"
+        k = c % n
+        m = size[c]
+        pos = np.full(m, c // n, np.int32)
+        kp.kv_append(pools[k], 0, x[c][:m], x[c][:m], bt[:m], pos, cu[:m + 1], stream=streams[k])
     torch.cuda.synchronize()
     for k, pool in enumerate(pools):
-        mine = x[k::n_streams]
-        n = mine.shape[0]
-        kk, vv = kp.kv_gather(pool, 0, bt, np.full(B, n, np.int32))
+        mine = x[k::n]
+        first = sum(s == B for s in size[k::n])  # calls that wrote the first B sequences only
+        kk, vv = kp.kv_gather(pool, 0, bt, np.full(big, mine.shape[0], np.int32))
         assert pool.device_error() == kp.KVP_OK
-        want = mine.transpose(0, 1).reshape(B * n, Hkv, d)
+        want = mine.transpose(0, 1).clone()
+        want[B:, :first] = 0
+        want = want.reshape(big * mine.shape[0], Hkv, d)
         assert torch.equal(kk, want) and torch.equal(vv, want)
         pool.close()
+    scratch.close()
