@@ -19,6 +19,8 @@
  *     work enqueued on `stream` has completed.  "host" arrays are read during the call only; the library
  *     keeps no reference to them after it returns.
  *   - `stream` is a hipStream_t (NULL = the legacy default stream).  Every call is asynchronous on it.
+ *     A stream under graph capture is refused (KVP_EHIP, nothing is enqueued) by the calls that read host arrays:
+ *     a graph would outlive their copies.  paged_decode_attn_noalloc can be captured.
  *   - Page ids read from device block tables are range-checked on the device.  An id outside
  *     [0, num_pages) is never dereferenced: the kernels skip that page and record KVP_ERANGE in the
  *     pool's device error word, which kv_pool_device_error() returns.  Such device-side errors are

@@ -70,6 +70,12 @@ struct HipRt {
   using Stream = hipStream_t;
   using Event = hipEvent_t;
   static hipError_t get_device(int* dev) { return hipGetDevice(dev); }
+  static hipError_t is_capturing(hipStream_t s, bool* capturing) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    const hipError_t e = hipStreamIsCapturing(s, &st);
+    *capturing = st != hipStreamCaptureStatusNone;
+    return e;
+  }
   static hipError_t event_create(hipEvent_t* ev) { return hipEventCreateWithFlags(ev, hipEventDisableTiming); }
   static void event_destroy(hipEvent_t ev) { (void)hipEventDestroy(ev); }
   static hipError_t event_record(hipEvent_t ev, hipStream_t s) { return hipEventRecord(ev, s); }

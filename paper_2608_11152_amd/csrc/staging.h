@@ -15,6 +15,7 @@
 //    destroyed with work pending and its handle given to a new one, and an event recorded later on that handle
 //    would not be behind the old stream's work; during a call the handle is the caller's.  (hipStreamPerThread,
 //    another stream in every thread, is among these.)
+// A capturing stream is refused: a graph would read the piece on every launch, long after it has been rewritten.
 #pragma once
 
 #include <algorithm>
@@ -27,7 +28,7 @@
 namespace kvp {
 
 // Rt: types Stream (the null stream is Stream{}), Event (Event{} is none), Error (0 is success), and
-//   get_device(int*), event_create(Event*), event_destroy(Event),
+//   get_device(int*), is_capturing(Stream, bool*), event_create(Event*), event_destroy(Event),
 //   event_record(Event, Stream), event_done(Event) -> bool, event_wait(Event), host_alloc(void**, size_t),
 //   host_free(void*), and the error sinks fail(code, format, ...) -> code and hip_fail(Error, what) -> code.
 template <class Rt>
@@ -44,7 +45,15 @@ class StagingOf {
     int dev = 0;
     auto e = Rt::get_device(&dev);
     if (e) return Rt::hip_fail(e, "hipGetDevice");
-    const bool shared = s == Stream{};  // the null stream: never destroyed
+    const bool shared = s == Stream{};  // the null stream: never destroyed, never capturing
+    if (!shared) {
+      bool capturing = false;
+      e = Rt::is_capturing(s, &capturing);
+      if (e) return Rt::hip_fail(e, "hipStreamIsCapturing");
+      if (capturing)
+        return Rt::fail(KVP_EHIP, "the stream is capturing a graph, which the call's metadata would not outlive "
+                        "(paged_decode_attn_noalloc can be captured)");
+    }
     n = (n + 255) & ~size_t(255);
     std::lock_guard<std::mutex> lock(mu_);
     int idx = -1;

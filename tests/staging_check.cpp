@@ -41,7 +41,7 @@ struct Sim {
   std::vector<std::shared_ptr<Queue>> queues;     // every queue that may hold work
   struct Event { uint64_t recorded = 0, reached = 0; std::shared_ptr<Queue> q; };
   std::map<int, Event> events;
-  int next_event = 1, device = 0, bad_stream = -1;
+  int next_event = 1, device = 0, capturing = -1, bad_stream = -1;
   int records = 0, waits = 0, pinned = 0;
   int last_fail = 0;
   std::map<void*, size_t> host;
@@ -67,6 +67,7 @@ struct SimRt {
   using Stream = int;
   using Event = int;
   static int get_device(int* d) { *d = sim->device; return 0; }
+  static int is_capturing(int s, bool* c) { *c = s == sim->capturing; return 0; }
   static int event_create(int* e) { *e = sim->next_event++; sim->events[*e]; return 0; }
   static void event_destroy(int e) { sim->events.erase(e); }
   static int event_record(int e, int s) {
@@ -197,6 +198,24 @@ void events_per_block() {
   w.drain();
 }
 
+// A capturing stream is refused and takes nothing; it and the others go on afterwards.
+void capture_refused() {
+  World w;
+  w.s.stream(3);
+  CHECK(w.call(3, 100) == KVP_OK);
+  w.drain();
+  const int records = w.s.records;
+  w.s.capturing = 3;
+  for (int c = 0; c < 50; ++c) {
+    Staging::Lease l;
+    CHECK(w.st.lease(100, 3, &l) == KVP_EHIP && l.slot < 0);
+  }
+  CHECK(w.s.records == records && w.s.handles[3]->ops.empty());
+  CHECK(w.call(0, 100) == KVP_OK);
+  w.s.capturing = -1;
+  for (int c = 0; c < 50; ++c) { CHECK(w.call(3, 100) == KVP_OK); w.drain(); }
+}
+
 // Launches that fail, on streams that take no event either, use up nothing.
 void failed_launches() {
   World w;
@@ -238,6 +257,7 @@ int main(int argc, char** argv) {
   recycled_handle();
   waits_when_behind();
   events_per_block();
+  capture_refused();
   failed_launches();
   concurrent_calls();
   for (unsigned k = 0; k < 40; ++k) random_calls(seed * 1000 + k, 300);
