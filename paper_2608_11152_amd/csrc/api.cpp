@@ -243,6 +243,33 @@ int build_chunks(const int32_t* cu_tokens, int num_seqs, std::vector<kvp::HashCh
   return KVP_OK;
 }
 
+// The chunks and, behind them, the first chunk of every sequence that has one, in a leased pinned piece.
+struct ChunkLists {
+  Staging::Lease lease;
+  const kvp::HashChunk* chunks = nullptr;
+  const int32_t* seq_first = nullptr;
+  int n_seqs = 0, longest = 0;  // the largest chunk count of a sequence
+};
+
+int lease_chunks(const std::vector<kvp::HashChunk>& chunks, hipStream_t s, ChunkLists* L) {
+  std::vector<int32_t> first;
+  for (size_t k = 0; k < chunks.size(); ++k)
+    if (chunks[k].c == 0) {
+      first.push_back((int32_t)k);
+      L->longest = std::max(L->longest, chunks[k].pad[0]);
+    }
+  const size_t nb = chunks.size() * sizeof(kvp::HashChunk);
+  const int rc = staging().lease(nb + first.size() * 4, s, &L->lease);
+  if (rc) return rc;
+  unsigned char* host = reinterpret_cast<unsigned char*>(L->lease.host);
+  std::memcpy(host, chunks.data(), nb);
+  std::memcpy(host + nb, first.data(), first.size() * 4);
+  L->chunks = reinterpret_cast<const kvp::HashChunk*>(host);
+  L->seq_first = reinterpret_cast<const int32_t*>(host + nb);
+  L->n_seqs = (int)first.size();
+  return KVP_OK;
+}
+
 // Page moves between the pool and the host tier: the item list is read by the kernel straight from a
 // pinned staging slot, released after the kernel.
 int run_tier(kvp_pool_t pool, int layer, const std::vector<kvp::TierItem>& items, void* host, int32_t* bt,
@@ -839,24 +866,17 @@ int kvp_block_hashes(const int32_t* tokens, const int32_t* cu_tokens, int num_se
   if (pages == 0) return KVP_OK;
   if (!tokens || !hashes) return set_err(KVP_EINVAL, "tokens or hashes is NULL");
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-  std::vector<int32_t> seq_first;
-  for (size_t k = 0; k < chunks.size(); ++k)
-    if (chunks[k].c == 0) seq_first.push_back((int32_t)k);
-  // pinned slot: [chunks | seq_first]
-  Staging::Lease lease;
-  const size_t nb = chunks.size() * sizeof(kvp::HashChunk);
-  int rc = staging().lease(nb + seq_first.size() * 4, s, &lease);
+  ChunkLists L;
+  int rc = lease_chunks(chunks, s, &L);
   if (rc) return rc;
-  unsigned char* host = reinterpret_cast<unsigned char*>(lease.host);
-  std::memcpy(host, chunks.data(), nb);
-  std::memcpy(host + nb, seq_first.data(), seq_first.size() * 4);
+  const Staging::Lease& lease = L.lease;
   kvp::HashArgs a{};
   a.tokens = tokens;
-  a.chunks = reinterpret_cast<const kvp::HashChunk*>(host);
+  a.chunks = L.chunks;
   a.seed = seed;
-  a.seq_first = reinterpret_cast<const int32_t*>(host + nb);
+  a.seq_first = L.seq_first;
   a.out = hashes;
-  const hipError_t e = kvp::launch_block_hash(a, (int)chunks.size(), (int)seq_first.size(), s);
+  const hipError_t e = kvp::launch_block_hash(a, (int)chunks.size(), L.n_seqs, L.longest, s);
   const int rr = staging().release(lease, e == hipSuccess);
   if (e != hipSuccess) return hip_err(e, "kvp_block_hashes launch");
   return rr;
@@ -922,7 +942,7 @@ int kvp_prefix_table_create(kvp_prefix_table_t* out, int capacity_log2) {
     a.keys = t->keys;
     a.vals = t->vals;
     a.mask = t->mask;
-    e = kvp::launch_table(a, 3, 0, nullptr);
+    e = kvp::launch_table(a, 3, nullptr);
   }
   if (e == hipSuccess) e = kvp::launch_fill_zero(t->err, 256, nullptr);
   if (e == hipSuccess) e = hipDeviceSynchronize();
@@ -954,7 +974,7 @@ int kvp_prefix_table_clear(kvp_prefix_table_t t, void* stream) {
   a.vals = t->vals;
   a.mask = t->mask;
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-  hipError_t e = kvp::launch_table(a, 3, 0, s);
+  hipError_t e = kvp::launch_table(a, 3, s);
   if (e == hipSuccess) e = kvp::launch_fill_zero(t->err, 256, s);
   return e == hipSuccess ? KVP_OK : hip_err(e, "kvp_prefix_table_clear launch");
 }
@@ -973,7 +993,7 @@ static int table_update(kvp_prefix_table_t t, const uint64_t* hashes, const int3
   a.pages = page_ids;
   a.n = n;
   a.err = t->err;
-  hipError_t e = kvp::launch_table(a, op, 0, reinterpret_cast<hipStream_t>(stream));
+  hipError_t e = kvp::launch_table(a, op, reinterpret_cast<hipStream_t>(stream));
   return e == hipSuccess ? KVP_OK : hip_err(e, "prefix table launch");
 }
 
@@ -1011,21 +1031,21 @@ int kvp_prefix_lookup(kvp_prefix_table_t t, const uint64_t* hashes, const int32_
       const int g0 = (int)k;
       for (size_t j = k; j < chunks.size() && chunks[j].pad[1] == chunks[k].pad[1]; ++j) chunks[j].g0 = g0;
     }
-  Staging::Lease lease;
-  const size_t nb = chunks.size() * sizeof(kvp::HashChunk);
-  rc = staging().lease(nb, s, &lease);
+  ChunkLists L;
+  rc = lease_chunks(chunks, s, &L);
   if (rc) return rc;
-  std::memcpy(lease.host, chunks.data(), nb);
+  const Staging::Lease& lease = L.lease;
   kvp::TableArgs a{};
   a.keys = t->keys;
   a.vals = t->vals;
   a.mask = t->mask;
   a.hashes = hashes;
-  a.chunks = reinterpret_cast<const kvp::HashChunk*>(lease.host);
+  a.chunks = L.chunks;
+  a.seq_first = L.seq_first;
   a.matched = matched_pages;
   a.out_pages = page_ids;
   a.err = t->err;
-  const hipError_t e = kvp::launch_table(a, 2, (int)chunks.size(), s);
+  const hipError_t e = kvp::launch_lookup(a, (int)chunks.size(), L.n_seqs, L.longest, s);
   const int rr = staging().release(lease, e == hipSuccess);
   if (e != hipSuccess) return hip_err(e, "kvp_prefix_lookup launch");
   return rr;

@@ -166,6 +166,7 @@ struct TableArgs {
   const int32_t* pages;     // insert / erase: [n]
   int64_t n;
   const HashChunk* chunks;  // lookup: 64-page chunks of the sequences (pinned host)
+  const int32_t* seq_first; // lookup: first chunk of each sequence (pinned host)
   int32_t* matched;         // lookup: [num_seqs]
   int32_t* out_pages;       // lookup: [total full pages]
   int* err;
@@ -185,9 +186,11 @@ hipError_t launch_decode_merge(const MergeArgs& a, int D, hipStream_t s);
 hipError_t launch_prefill(const PrefillArgs& a, int D, hipStream_t s);
 hipError_t launch_prefill_long(const PrefillArgs& a, hipStream_t s);  // launch_prefill with long_items
 hipError_t launch_tier(const TierArgs& a, bool restore, hipStream_t s);
-hipError_t launch_block_hash(const HashArgs& a, int n_chunks, int n_seqs, hipStream_t s);  // n_seqs: with a chunk
+// n_seqs: sequences with a chunk; longest: the largest chunk count of a sequence
+hipError_t launch_block_hash(const HashArgs& a, int n_chunks, int n_seqs, int longest, hipStream_t s);
+hipError_t launch_lookup(const TableArgs& a, int n_chunks, int n_seqs, int longest, hipStream_t s);
 hipError_t launch_group_lcp(const GroupLcpArgs& a, int n_groups, hipStream_t s);
-// op: 0 insert, 1 erase, 2 lookup, 3 clear
-hipError_t launch_table(const TableArgs& a, int op, int n_seqs, hipStream_t s);
+// op: 0 insert, 1 erase, 3 clear
+hipError_t launch_table(const TableArgs& a, int op, hipStream_t s);
 
 }  // namespace kvp

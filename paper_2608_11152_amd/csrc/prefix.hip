@@ -42,6 +42,11 @@ __device__ __forceinline__ uint64_t shfl_up64(uint64_t v, int d) {
   return ((uint64_t)hi << 32) | lo;
 }
 
+__device__ __forceinline__ uint64_t shfl64(uint64_t v, int src) {
+  const unsigned lo = __shfl((unsigned)v, src), hi = __shfl((unsigned)(v >> 32), src);
+  return ((uint64_t)hi << 32) | lo;
+}
+
 __device__ __forceinline__ uint64_t table_key(uint64_t h) { return h ? h : 1ull; }
 
 // Inclusive scan over the 64 lanes of the affine maps h -> A*h + B (lane j ends with the composition of
@@ -59,6 +64,8 @@ __device__ __forceinline__ void affine_scan(uint64_t& A, uint64_t& B, int lane) 
 
 // Pass 1: one wave per 64-page chunk.  Lane j folds its page's tokens; the scan gives the chunk-local
 // chain value B_j (the chain started from 0 at the chunk's first page), kept in the output slot.
+// LONG: B_0 in the first slot, in the others B_j without the first page's part.
+template <bool LONG>
 __global__ __launch_bounds__(64) void hash_chunk_kernel(HashArgs a) {
   const HashChunk ch = a.chunks[blockIdx.x];
   const int lane = threadIdx.x;
@@ -75,6 +82,10 @@ __global__ __launch_bounds__(64) void hash_chunk_kernel(HashArgs a) {
     B = x;
   }
   affine_scan(A, B, lane);
+  if constexpr (LONG) {
+    const uint64_t pa = shfl_up64(A, 1), b0 = shfl64(B, 0);
+    if (lane > 0) B -= pa * b0;
+  }
   if (lane < ch.n) a.out[ch.o0 + lane] = B;
 }
 
@@ -90,25 +101,38 @@ __device__ __forceinline__ uint64_t gamma_pow(unsigned e) {  // by squaring
 // Pass 2: one 16-wave workgroup per sequence, kFinishChunks chunks at a time.  Thread i scans chunk i's map
 // (gamma^n, its last page's B) into the chain value entering the chunk; once all have read, the waves take the
 // chunks in turn and lane j finishes hash = mix(gamma^(j+1) * entering + B_j) in place.
+// LONG (calls with a sequence of more than kLongChunks chunks, whose pages are too much work for one workgroup):
+// the threads put the chain value V_0 behind each chunk's first page into its slot, which no other chunk reads,
+// and a third pass of one wave per chunk finishes mix(V_0), mix(gamma^j * V_0 + the slot).
 constexpr int kFinishChunks = 1024;
+// Where the lines lie (us a call, two passes -> three; one sequence unless said): hashes 131,072 tokens (128 chunks)
+// 21.2 -> 25.0, 256 chunks 20.8 -> 21.6, 391: 26.0 -> 22.3, 1024: 51.2 -> 24.1, 4 x 1024: 61.6 -> 42.7, 4096:
+// 173 -> 58; lookup 128 chunks 27.4 -> 29.9, 1024: 25.8 -> 29.4, 4 x 1024: 41.9 -> 42.3, 4096: 56.6 -> 44.9,
+// 16,384: 520 -> 143.
+constexpr int kLongChunks = 256, kLongLookupChunks = 1536;
 constexpr int kFinishWaves = kFinishChunks / 64;
 
+template <bool LONG>
 __global__ __launch_bounds__(kFinishChunks) void hash_finish_kernel(HashArgs a) {
-  __shared__ uint64_t enter[kFinishChunks];
+  __shared__ uint64_t enter[LONG ? 1 : kFinishChunks];
   __shared__ uint64_t wave_a[kFinishWaves], wave_b[kFinishWaves];
   const HashChunk first = a.chunks[a.seq_first[blockIdx.x]];  // a sequence's first chunk
   const int nch = first.pad[0], np = first.pad[2];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   uint64_t* out = a.out + first.o0;
-  const uint64_t g_lane = gamma_pow((unsigned)lane + 1), g_chunk = gamma_pow(64);
+  const uint64_t g_lane = gamma_pow((unsigned)lane + 1), g_chunk = gamma_pow(64), g_63 = gamma_pow(63);
   uint64_t carry = a.seed;  // the chain value entering chunk c0
   for (int c0 = 0; c0 < nch; c0 += kFinishChunks) {
     const int c = c0 + (int)threadIdx.x;
     const int n = min(64, np - 64 * c);  // chunk c's pages (<= 0 past the end)
-    uint64_t A = 1, B = 0;
+    uint64_t A = 1, B = 0, b0 = 0;
     if (n > 0) {
       A = n == 64 ? g_chunk : gamma_pow((unsigned)n);
       B = out[64 * (int64_t)c + n - 1];
+      if constexpr (LONG) {
+        b0 = out[64 * (int64_t)c];
+        if (n > 1) B += (n == 64 ? g_63 : gamma_pow((unsigned)n - 1)) * b0;
+      }
     }
     affine_scan(A, B, lane);
     if (lane == 63) {
@@ -129,8 +153,14 @@ __global__ __launch_bounds__(kFinishChunks) void hash_finish_kernel(HashArgs a) 
     // entering chunk c: the chunks before it in the wave (lane - 1's inclusive scan) after those waves
     const uint64_t pa = shfl_up64(A, 1), pb = shfl_up64(B, 1);
     const uint64_t at_wave = ha * carry + hb;
-    enter[threadIdx.x] = lane == 0 ? at_wave : pa * at_wave + pb;
+    const uint64_t at_chunk = lane == 0 ? at_wave : pa * at_wave + pb;
     carry = ta * carry + tb;
+    if constexpr (LONG) {
+      if (n > 0) out[64 * (int64_t)c] = kGamma * at_chunk + b0;
+      __syncthreads();
+      continue;
+    }
+    enter[LONG ? 0 : threadIdx.x] = at_chunk;
     __syncthreads();
     const int here = min(kFinishChunks, nch - c0);
     for (int k0 = w; k0 < here; k0 += 4 * kFinishWaves) {
@@ -148,6 +178,15 @@ __global__ __launch_bounds__(kFinishChunks) void hash_finish_kernel(HashArgs a) 
     }
     __syncthreads();
   }
+}
+
+// Pass 3 of calls with a long sequence: one wave per chunk.
+__global__ __launch_bounds__(64) void hash_pages_kernel(HashArgs a) {
+  const HashChunk ch = a.chunks[blockIdx.x];
+  const int lane = threadIdx.x;
+  const uint64_t v = lane < ch.n ? a.out[ch.o0 + lane] : 0;
+  const uint64_t v0 = shfl64(v, 0);
+  if (lane < ch.n) a.out[ch.o0 + lane] = mix64(lane == 0 ? v : gamma_pow((unsigned)lane) * v0 + v);
 }
 
 // One 64-lane workgroup per group: the number of leading pages on which every member's block hash
@@ -264,6 +303,45 @@ __global__ __launch_bounds__(64) void lookup_finish_kernel(TableArgs a) {
   if (lane == 0) a.matched[ch.pad[1]] = matched;
 }
 
+// Lookup pass 2 of calls with a long sequence: one workgroup per sequence finds the earliest miss and reports the
+// prefix's length; pass 3, one wave per chunk, reports the pages behind it as -1.
+constexpr int kMissThreads = 1024;
+
+__global__ __launch_bounds__(kMissThreads) void lookup_miss_kernel(TableArgs a) {
+  __shared__ int first;  // the earliest chunk with a miss
+  const HashChunk ch = a.chunks[a.seq_first[blockIdx.x]];
+  const int nch = ch.pad[0], np = ch.pad[2];
+  const int32_t* out = a.out_pages + ch.o0;
+  if (threadIdx.x == 0) first = INT32_MAX;
+  __syncthreads();
+  for (int c0 = 0; c0 < nch && np > 0; c0 += 4 * kMissThreads) {
+    int at = INT32_MAX;
+#pragma unroll
+    for (int u = 3; u >= 0; --u) {
+      const int c = c0 + u * kMissThreads + (int)threadIdx.x;
+      if (c < nch && out[min(64 * (int64_t)c + 63, (int64_t)np - 1)] < 0) at = c;
+    }
+    if (at != INT32_MAX) atomicMin(&first, at);
+    __syncthreads();
+    const bool found = first != INT32_MAX;
+    __syncthreads();
+    if (found) break;
+  }
+  if (threadIdx.x >= 64) return;
+  int matched = np;
+  if (first != INT32_MAX) {
+    const int64_t p = 64 * (int64_t)first + threadIdx.x;
+    matched = 64 * first + (int)__builtin_ctzll(__ballot(p < np && out[p] < 0));
+  }
+  if (threadIdx.x == 0) a.matched[ch.pad[1]] = matched;
+}
+
+__global__ __launch_bounds__(64) void lookup_cut_kernel(TableArgs a) {
+  const HashChunk ch = a.chunks[blockIdx.x];
+  const int lane = threadIdx.x;
+  if (lane < ch.n && 64 * ch.c + lane >= a.matched[ch.pad[1]]) a.out_pages[ch.o0 + lane] = -1;
+}
+
 __global__ void fill_table_kernel(uint64_t* keys, int32_t* vals, int64_t n) {
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
@@ -274,12 +352,18 @@ __global__ void fill_table_kernel(uint64_t* keys, int32_t* vals, int64_t n) {
 
 }  // namespace
 
-hipError_t launch_block_hash(const HashArgs& a, int n_chunks, int n_seqs, hipStream_t s) {
+hipError_t launch_block_hash(const HashArgs& a, int n_chunks, int n_seqs, int longest, hipStream_t s) {
   if (n_chunks == 0) return hipSuccess;
-  hipLaunchKernelGGL(hash_chunk_kernel, dim3(n_chunks), dim3(64), 0, s, a);
+  const bool lng = longest > kLongChunks;
+  if (lng) hipLaunchKernelGGL(hash_chunk_kernel<true>, dim3(n_chunks), dim3(64), 0, s, a);
+  else hipLaunchKernelGGL(hash_chunk_kernel<false>, dim3(n_chunks), dim3(64), 0, s, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(hash_finish_kernel, dim3(n_seqs), dim3(kFinishChunks), 0, s, a);
+  if (lng) hipLaunchKernelGGL(hash_finish_kernel<true>, dim3(n_seqs), dim3(kFinishChunks), 0, s, a);
+  else hipLaunchKernelGGL(hash_finish_kernel<false>, dim3(n_seqs), dim3(kFinishChunks), 0, s, a);
+  e = hipGetLastError();
+  if (e != hipSuccess || !lng) return e;
+  hipLaunchKernelGGL(hash_pages_kernel, dim3(n_chunks), dim3(64), 0, s, a);
   return hipGetLastError();
 }
 
@@ -289,18 +373,28 @@ hipError_t launch_group_lcp(const GroupLcpArgs& a, int n_groups, hipStream_t s) 
   return hipGetLastError();
 }
 
-hipError_t launch_table(const TableArgs& a, int op, int n_seqs, hipStream_t s) {
+hipError_t launch_lookup(const TableArgs& a, int n_chunks, int n_seqs, int longest, hipStream_t s) {
+  if (n_chunks == 0) return hipSuccess;
+  hipLaunchKernelGGL(lookup_chunk_kernel, dim3(n_chunks), dim3(64), 0, s, a);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  if (longest <= kLongLookupChunks) {
+    hipLaunchKernelGGL(lookup_finish_kernel, dim3(n_chunks), dim3(64), 0, s, a);
+    return hipGetLastError();
+  }
+  hipLaunchKernelGGL(lookup_miss_kernel, dim3(n_seqs), dim3(kMissThreads), 0, s, a);
+  e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(lookup_cut_kernel, dim3(n_chunks), dim3(64), 0, s, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_table(const TableArgs& a, int op, hipStream_t s) {
   if (op == 0 || op == 1) {
     if (a.n == 0) return hipSuccess;
     const dim3 grid((unsigned)((a.n + 255) / 256));
     if (op == 0) hipLaunchKernelGGL(table_insert_kernel, grid, dim3(256), 0, s, a);
     else hipLaunchKernelGGL(table_erase_kernel, grid, dim3(256), 0, s, a);
-  } else if (op == 2) {
-    if (n_seqs == 0) return hipSuccess;  // n_seqs: chunk count here
-    hipLaunchKernelGGL(lookup_chunk_kernel, dim3(n_seqs), dim3(64), 0, s, a);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(lookup_finish_kernel, dim3(n_seqs), dim3(64), 0, s, a);
   } else {
     hipLaunchKernelGGL(fill_table_kernel, dim3(1024), dim3(256), 0, s, a.keys, a.vals, (int64_t)a.mask + 1);
   }
