@@ -62,19 +62,20 @@ __global__ __launch_bounds__(256) void decode_kernel(DecodeArgs a) {
 // with a running max, and the T lanes are then combined by shuffles.
 // Bound: latency of the rounds of 16 loads.  One sequence of 131,007 tokens has 512 partials: whole head
 // rows (T = 8, 4 rounds, 32 workgroups) took 19.1 us and the call 72.1 us, quarter rows (T = 32, 1 round, 128
-// workgroups) take the call to 61.2 us.
+// workgroups) take the call to 61.2 us.  DSPLIT is a template argument: read from the arguments, the divisions by
+// it cost the calls that do not split 9% (2048 rows x 16 heads of 2 partials 85.8 -> 93.8 us).
 // ---------------------------------------------------------------------------------------------------
 constexpr int kMergeInFlight = 16;  // partials in flight per lane
 
-template <int D>
+template <int D, int DSPLIT>
 __global__ __launch_bounds__(256) void decode_merge_kernel(MergeArgs a) {
   constexpr int U = kMergeInFlight;
-  const int V4 = D / 4 / a.dsplit;  // float4 per head row of this workgroup
+  constexpr int V4 = D / 4 / DSPLIT;  // float4 per head row of this workgroup
   const int G = a.Hq / a.Hkv;
   const int hw = a.hw;
   const int nsplit = G / hw;
-  const int dsub = blockIdx.x % a.dsplit;
-  const int b = blockIdx.x / a.dsplit;
+  const int dsub = (int)(blockIdx.x % DSPLIT);
+  const int b = (int)(blockIdx.x / DSPLIT);
   const int rest = b / nsplit;
   const int sub = b - rest * nsplit;
   const int grp = rest / a.Hkv;
@@ -206,6 +207,13 @@ hipError_t launch_decode(const DecodeArgs& a, int D, hipStream_t s) {
   return hipGetLastError();
 }
 
+template <int D>
+static void launch_merge_kernel(const MergeArgs& m, int dsplit, dim3 grid, hipStream_t s) {
+  if (dsplit == 1) hipLaunchKernelGGL((decode_merge_kernel<D, 1>), grid, dim3(256), 0, s, m);
+  else if (dsplit == 2) hipLaunchKernelGGL((decode_merge_kernel<D, 2>), grid, dim3(256), 0, s, m);
+  else hipLaunchKernelGGL((decode_merge_kernel<D, 4>), grid, dim3(256), 0, s, m);
+}
+
 hipError_t launch_decode_merge(const MergeArgs& a, int D, hipStream_t s) {
   if (a.n_merge == 0) return hipSuccess;
   // Split the query heads of a (sequence, KV head) over up to G workgroups while the grid stays at or
@@ -218,13 +226,13 @@ hipError_t launch_decode_merge(const MergeArgs& a, int D, hipStream_t s) {
   while (2 * nsplit <= G && (units * 2 * nsplit <= 1024 || G / nsplit > 1024 / D)) nsplit *= 2;
   MergeArgs m = a;
   m.hw = G / nsplit;
-  m.dsplit = 1;
-  while (m.dsplit < 4 && m.hw == 1 && units * nsplit * m.dsplit * 2 <= 1024 &&
-         a.max_parts > kMergeInFlight * (1024 / D) * m.dsplit)
-    m.dsplit *= 2;
-  const dim3 grid((unsigned)(units * nsplit * m.dsplit));
-  if (D == 128) hipLaunchKernelGGL(decode_merge_kernel<128>, grid, dim3(256), 0, s, m);
-  else hipLaunchKernelGGL(decode_merge_kernel<64>, grid, dim3(256), 0, s, m);
+  int dsplit = 1;
+  while (dsplit < 4 && m.hw == 1 && units * nsplit * dsplit * 2 <= 1024 &&
+         a.max_parts > kMergeInFlight * (1024 / D) * dsplit)
+    dsplit *= 2;
+  const dim3 grid((unsigned)(units * nsplit * dsplit));
+  if (D == 128) launch_merge_kernel<128>(m, dsplit, grid, s);
+  else launch_merge_kernel<64>(m, dsplit, grid, s);
   return hipGetLastError();
 }
 

@@ -92,7 +92,6 @@ struct MergeArgs {
   int Hq, Hkv;
   int max_parts;              // largest partial count of a record
   int hw;                     // query heads per merge workgroup (set by launch_decode_merge)
-  int dsplit;                 // workgroups a head row is split over (set by launch_decode_merge)
 };
 
 struct PrefillArgs {
