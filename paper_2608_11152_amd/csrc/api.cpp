@@ -501,7 +501,7 @@ kvp::PrefillArgs prefill_args(const PrefillLayout& L, kvp_pool_t pool, int layer
   a.items = reinterpret_cast<const kvp::PrefillWork*>(meta + L.off_items);
   a.n_items = (int)L.plan.items.size();
   const int64_t stages = kvp::prefill_mean_stages(L.plan);
-  a.long_items = pool->dtype == KVP_BF16 && pool->head_dim == 128 && stages >= kvp::kPrefillLongStages;
+  a.long_items = kvp::prefill_long(pool->dtype == KVP_BF16, pool->head_dim, num_q_heads / pool->num_kv_heads, stages);
   a.half_tiles = stages < kvp::kPrefillHalfTileStages;
   a.zero = reinterpret_cast<const unsigned char*>(pool->err) + kErrLine;
   a.part_acc = reinterpret_cast<float*>(w + L.off_acc);

@@ -101,7 +101,7 @@ struct PrefillArgs {
   int maxp;
   const PrefillWork* items;
   int n_items;
-  bool long_items;          // the kernel for long key ranges (kPrefillLongStages)
+  bool long_items;          // the kernel for long key ranges (prefill_long)
   bool half_tiles;          // the other kernel: a workgroup per half tile
   const unsigned char* zero;  // one (page, head) block of zeros, read in the place of a page outside the pool
   float* part_acc;          // [parts, Hq, D] unnormalised accumulators of split tiles

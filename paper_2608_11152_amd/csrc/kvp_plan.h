@@ -112,10 +112,16 @@ constexpr int kPrefillRows = 32 * kPrefillWaves;    // flattened query rows per 
 // A call whose tiles (x their 64-key stages) would not give about this many equal workgroups splits
 // tile histories into key ranges: the resident prefill workgroups of 256 CUs (8 waves per CU).
 constexpr int kPrefillSplitTarget = 256 * 8 / kPrefillWaves;
-// Items of at least this many stages on average go to the kernel for long key ranges (bf16 pages, d = 128).
-// Both sides measured, that kernel's time over the other's: 12.5 stages 1.05, 16: 1.01, 18: 0.99 (300-token chunks
-// over 2k: 36 stages 0.99), 20.5: 0.98, 32: 0.94, 64: 0.91-0.93, 130: 0.93, 1400: 0.91.
-constexpr int kPrefillLongStages = 18;
+// Items of at least this many stages on average go to the kernel for long key ranges (bf16 pages, d = 128).  Its
+// start must be paid back by what it saves per stage, which is the less the fewer query rows read each page: with
+// fewer than 8 query heads per KV head more of a stage is the page itself.  700 calls of 1-32 sessions, chunks of
+// 4-2048 tokens, histories of 200-65536 and 1-16 KV heads, that kernel's time over the other's (median, most):
+//   8 or 16 heads: 18-30 stages 1.09, 1.19; 30-52: 1.02, 1.11; 52-64: 0.99, 1.04; 64-100: 0.97, 1.02; 100+: 0.94, 0.98
+//   1, 2 or 4:     18-30 stages 1.12, 1.41; 30-52: 1.05, 1.14; 52-96: 1.01, 1.12; 96-150: 0.97, 1.00; 150+: 0.95, 0.99
+constexpr int kPrefillLongStages = 64, kPrefillLongStagesFewHeads = 96;
+inline bool prefill_long(bool bf16, int D, int G, int64_t mean_stages) {
+  return bf16 && D == 128 && mean_stages >= (G >= 8 ? kPrefillLongStages : kPrefillLongStagesFewHeads);
+}
 // In the other kernel, items of fewer stages than this on average get a workgroup per half tile (twice the
 // staging, but two workgroups on a CU overlap their starts and outputs).  Whole tiles' time over half tiles',
 // d = 128: 2 stages 1.12, 4.5: 1.04, 8 (36 items) 1.10, 8 (128 items) 1.00, 8.5: 0.99, FP8 pages 12.5: 0.99, 68: 0.94.

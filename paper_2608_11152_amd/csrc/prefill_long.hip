@@ -19,7 +19,8 @@
 //  * Pages go from the pool straight to LDS, two stages ahead in a ring of four (through registers: 16.8 ms).
 // Measured (MI355X): eight 2048-token chunks over 32k-131k histories 17.9 -> 16.3 ms (1.14 -> 1.25 PFLOP/s),
 // a 64-token chunk over 131k 157 -> 147 us; the start costs about 10 us more per workgroup (queries for 64 rows
-// per wave, the first and last half not interleaved), hence the rule in kvp_plan.h.
+// per wave, the first and last half not interleaved; there and at the end the compiler spills 34 VGPRs, 140 bytes a
+// lane, none in the pipelined loop), hence the rule in kvp_plan.h.
 #include <type_traits>
 #include <utility>
 

@@ -286,6 +286,30 @@ static bool run_prefill(const PrefillCase& c) {
   return check_prefill(c, P);
 }
 
+// The prefill kernel a call gets: where the kernel for long key ranges was measured slower than the other, it must
+// not be chosen, and long ranges must go to it.
+static bool run_prefill_rule() {
+  struct R { int Hq, Hkv, sessions, chunk, ctx; bool is_long; };
+  static const R rules[] = {
+      {16, 16, 16, 512, 1000, false}, {16, 16, 8, 256, 2000, false}, {16, 16, 16, 512, 2000, false},
+      {16, 16, 4, 256, 8000, false},  {32, 4, 16, 512, 1000, false}, {32, 4, 8, 8, 16000, false},
+      {32, 8, 16, 8, 4000, false},    {32, 8, 16, 512, 2000, false}, {32, 4, 1, 64, 131072, true},
+      {32, 4, 8, 2048, 65536, true},  {32, 8, 8, 512, 32000, true},  {16, 16, 4, 512, 32000, true},
+  };
+  for (const R& r : rules) {
+    std::vector<int32_t> ctx(r.sessions, r.ctx), cuq(r.sessions + 1, 0);
+    for (int i = 0; i < r.sessions; ++i) cuq[i + 1] = cuq[i] + r.chunk;
+    PrefillPlan P;
+    EXPECT(kvp::plan_prefill(ctx.data(), cuq.data(), r.sessions, 1 << 20, r.Hq, r.Hkv, &P).ok(), "rule plan");
+    const int64_t st = kvp::prefill_mean_stages(P);
+    EXPECT(kvp::prefill_long(true, 128, r.Hq / r.Hkv, st) == r.is_long, "%d x %d over %d (GQA %d/%d): %lld stages",
+           r.sessions, r.chunk, r.ctx, r.Hq, r.Hkv, (long long)st);
+    EXPECT(!kvp::prefill_long(false, 128, r.Hq / r.Hkv, st) && !kvp::prefill_long(true, 64, r.Hq / r.Hkv, st),
+           "only bf16 pages with d = 128");
+  }
+  return true;
+}
+
 static bool run_errors() {
   DecodeCase c;
   c.lens = {40, 50};
@@ -407,7 +431,7 @@ int main(int argc, char** argv) {
   if (argc > 1 && !std::strcmp(argv[1], "self-test")) return self_test() ? 0 : 1;
   const int iters = argc > 1 ? std::atoi(argv[1]) : 200;
   rng.seed(argc > 2 ? std::strtoull(argv[2], nullptr, 10) : 12345);
-  if (!run_errors()) return 1;
+  if (!run_errors() || !run_prefill_rule()) return 1;
   for (int k = 0; k < iters; ++k) {
     if (!run_decode(random_decode())) {
       std::fprintf(stderr, "decode case %d\n", k);

@@ -29,7 +29,7 @@ def _reference(q, k, v, ctx, scale):
     return out
 
 
-# 256 (session, KV head) tiles: no history is split, each item has 40 stages or more.
+# 256 (session, KV head) tiles: no history is split, each item has 96 stages or more.
 @pytest.mark.parametrize("G,Hkv,chunks", [(8, 8, [1, 2, 15, 16, 17, 31, 32]), (16, 8, [1, 3, 15, 16]),
                                           (1, 8, [1, 63, 64, 65, 200, 256]), (2, 8, [1, 127, 128]),
                                           (4, 8, [5, 33, 64])])
@@ -37,7 +37,7 @@ def _reference(q, k, v, ctx, scale):
 def test_long_ranges(G, Hkv, chunks, out_dtype):
     import torch
     n_seq = 256 // Hkv
-    ctx = [2560 + x for x in ([0, 1, 15, 16, 17, 30, 31, 32, 33, 46, 47, 48, 49, 62, 63, 64] * 2)][:n_seq]
+    ctx = [6144 + x for x in ([0, 1, 15, 16, 17, 30, 31, 32, 33, 46, 47, 48, 49, 62, 63, 64] * 2)][:n_seq]
     new = [chunks[i % len(chunks)] for i in range(n_seq)]
     pages = [(a + b + 15) // 16 for a, b in zip(ctx, new)]
     g = torch.Generator(device="cuda")
@@ -78,7 +78,7 @@ def test_long_range_page_outside_the_pool():
     """The page counts as zeros (keys and values), the call reports KVP_ERANGE, and stale values past the end of the
     sequence (here infinities) do not reach the output."""
     import torch
-    n, C, Hkv, G = 2565, 5, 8, 8
+    n, C, Hkv, G = 6149, 5, 8, 8
     n_seq = 32
     pages = (n + C + 15) // 16
     g = torch.Generator(device="cuda")
