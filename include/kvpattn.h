@@ -238,7 +238,9 @@ int mixed_step_workspace_size(kvp_pool_t pool, const int32_t* seq_lens, int num_
 /* paged_decode_attn(q_dec, pool, layer, block_tables_dec, maxp_dec, seq_lens, num_dec, group_prefix,
  * num_q_heads, scale, out_dec, out_dtype, ...) and prefix_chunk_prefill_attn(q_pf, pool, layer,
  * block_tables_pf, maxp_pf, ctx_lens, cu_q, num_pf, num_q_heads, scale, out_pf, out_dtype, ...) in one
- * call on one stream: the decode kernel, the prefill kernel behind it, then the merges of either part's
+ * call on one stream.  The two parts share one launch (the decode work first, the prefill workgroups take the compute
+ * units as the decode's retire; shared-prefix ranges that the plan stages through LDS run ahead of it), or the decode
+ * kernel and behind it the prefill kernel where that is the one for long key ranges; then the merges of either part's
  * split-KV partials.  Arguments, layouts and errors are those
  * of the two calls (num_dec = 0 or num_pf = 0 leaves that part out); both parts read one pool and layer,
  * and the prefill chunks' K/V must already have been appended.  Outputs are bitwise identical to the two

@@ -1222,8 +1222,12 @@ int mixed_step_attn(kvp_pool_t pool, int layer, int num_q_heads, float scale, in
     p = prefill_args(L.pf, pool, layer, q_pf, block_tables_pf, maxp_pf, num_q_heads, scale, out_pf, out_dtype,
                      meta_pf, w + L.off_pf);
   }
-  if (num_dec > 0) e = kvp::launch_decode(d, pool->head_dim, s);
-  if (e == hipSuccess && has_pf) e = kvp::launch_prefill(p, pool->head_dim, s);
+  if (num_dec > 0 && has_pf && !p.long_items) {
+    e = kvp::launch_mixed_step(d, p, pool->head_dim, s);
+  } else {
+    if (num_dec > 0) e = kvp::launch_decode(d, pool->head_dim, s);
+    if (e == hipSuccess && has_pf) e = kvp::launch_prefill(p, pool->head_dim, s);
+  }
   if (e == hipSuccess && num_dec > 0)
     e = launch_merge(reinterpret_cast<const int32_t*>(reinterpret_cast<const unsigned char*>(lease.host) +
                                                       L.dec.off_merge),

@@ -1,6 +1,6 @@
 // Device code of the paged decode path: the split-KV wave chunks, the LDS-staged shared-prefix
-// blocks and the block-level entry points the kernels of decode.hip call (bf16 and FP8 pages); everything
-// here is inline.
+// blocks and the block-level entry points the kernels of decode.hip and mixed.hip call (bf16 and FP8 pages);
+// everything here is inline.
 #pragma once
 
 #include "kvp_kernels.h"

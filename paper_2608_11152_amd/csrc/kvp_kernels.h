@@ -184,6 +184,8 @@ hipError_t launch_put_bytes(void* dst, const void* src, size_t n, hipStream_t s)
 hipError_t launch_decode_merge(const MergeArgs& a, int D, hipStream_t s);
 hipError_t launch_prefill(const PrefillArgs& a, int D, hipStream_t s);
 hipError_t launch_prefill_long(const PrefillArgs& a, hipStream_t s);  // launch_prefill with long_items
+// Both parts of a mixed step whose prefill is not long_items (the decode's work without its merge).
+hipError_t launch_mixed_step(const DecodeArgs& d, const PrefillArgs& p, int D, hipStream_t s);
 hipError_t launch_tier(const TierArgs& a, bool restore, hipStream_t s);
 // n_seqs: sequences with a chunk; longest: the largest chunk count of a sequence
 hipError_t launch_block_hash(const HashArgs& a, int n_chunks, int n_seqs, int longest, hipStream_t s);

@@ -1,4 +1,4 @@
-// Device helpers shared by the prefill kernels (prefill.hip, prefill_long.hip); everything here is inline.
+// Device helpers shared by the prefill kernels (prefill.hip, prefill_long.hip, mixed.hip); everything here is inline.
 #pragma once
 
 #include "kvp_kernels.h"
