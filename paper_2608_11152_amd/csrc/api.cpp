@@ -221,9 +221,10 @@ int lease_seq_info(const int32_t* cu_tokens, int num_seqs, hipStream_t s, Stagin
   return KVP_OK;
 }
 
-// 64-page chunks of every sequence's full pages (block hashing and prefix lookup work per chunk);
-// pad = {the sequence's chunk count, the sequence, its full pages}.
-int build_chunks(const int32_t* cu_tokens, int num_seqs, std::vector<kvp::HashChunk>* chunks, int64_t* pages) {
+// 64-page chunks of every sequence's full pages (block hashing and prefix lookup work per chunk).
+// `every`: a sequence without a full page has an empty chunk.
+int build_chunks(const int32_t* cu_tokens, int num_seqs, bool every, std::vector<kvp::HashChunk>* chunks,
+                 int64_t* pages) {
   if (!cu_tokens) return set_err(KVP_EINVAL, "cu_tokens is NULL");
   if (cu_tokens[0] != 0) return set_err(KVP_EINVAL, "cu_tokens[0] = %d, must be 0", cu_tokens[0]);
   int64_t tot = 0;
@@ -231,11 +232,10 @@ int build_chunks(const int32_t* cu_tokens, int num_seqs, std::vector<kvp::HashCh
     const int32_t n = cu_tokens[i + 1] - cu_tokens[i];
     if (n < 0) return set_err(KVP_EINVAL, "cu_tokens decreases at %d", i);
     const int np = n / kvp::kPage;
-    const int g0 = (int)chunks->size();
-    const int nch = (np + 63) / 64;
+    const int nch = std::max((np + 63) / 64, every ? 1 : 0);
     for (int c = 0; c < nch; ++c)
       chunks->push_back(kvp::HashChunk{cu_tokens[i] + 64 * kvp::kPage * c, (int32_t)(tot + 64 * c),
-                                       std::min(64, np - 64 * c), c, g0, {nch, i, np}});
+                                       std::min(64, np - 64 * c), c, nch, i, np, 0});
     tot += np;
     if (tot > INT32_MAX) return set_err(KVP_EINVAL, "more than 2^31 pages");
   }
@@ -256,7 +256,7 @@ int lease_chunks(const std::vector<kvp::HashChunk>& chunks, hipStream_t s, Chunk
   for (size_t k = 0; k < chunks.size(); ++k)
     if (chunks[k].c == 0) {
       first.push_back((int32_t)k);
-      L->longest = std::max(L->longest, chunks[k].pad[0]);
+      L->longest = std::max(L->longest, chunks[k].n_chunks);
     }
   const size_t nb = chunks.size() * sizeof(kvp::HashChunk);
   const int rc = staging().lease(nb + first.size() * 4, s, &L->lease);
@@ -861,7 +861,7 @@ int kvp_block_hashes(const int32_t* tokens, const int32_t* cu_tokens, int num_se
   if (num_seqs == 0) return KVP_OK;
   std::vector<kvp::HashChunk> chunks;
   int64_t pages = 0;
-  int rc0 = build_chunks(cu_tokens, num_seqs, &chunks, &pages);
+  int rc0 = build_chunks(cu_tokens, num_seqs, false, &chunks, &pages);
   if (rc0) return rc0;
   if (pages == 0) return KVP_OK;
   if (!tokens || !hashes) return set_err(KVP_EINVAL, "tokens or hashes is NULL");
@@ -1015,22 +1015,11 @@ int kvp_prefix_lookup(kvp_prefix_table_t t, const uint64_t* hashes, const int32_
   if (!matched_pages) return set_err(KVP_EINVAL, "matched_pages is NULL");
   std::vector<kvp::HashChunk> chunks;
   int64_t pages = 0;
-  int rc = build_chunks(cu_tokens, num_seqs, &chunks, &pages);
+  // (sequences without a full page match nothing: pass 2 reports 0 for their empty chunk)
+  int rc = build_chunks(cu_tokens, num_seqs, true, &chunks, &pages);
   if (rc) return rc;
   if (pages > 0 && (!hashes || !page_ids)) return set_err(KVP_EINVAL, "hashes or page_ids is NULL");
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-  // Sequences without a full page match nothing: give them a zero-length chunk so pass 2 reports 0.
-  for (int i = 0, k = 0; i < num_seqs; ++i) {
-    while (k < (int)chunks.size() && chunks[k].pad[1] < i) ++k;
-    if (k == (int)chunks.size() || chunks[k].pad[1] != i) {
-      chunks.insert(chunks.begin() + k, kvp::HashChunk{0, 0, 0, 0, 0, {1, i, 0}});
-    }
-  }
-  for (size_t k = 0; k < chunks.size(); ++k)  // g0 must index this sequence's first chunk after inserts
-    if (chunks[k].c == 0) {
-      const int g0 = (int)k;
-      for (size_t j = k; j < chunks.size() && chunks[j].pad[1] == chunks[k].pad[1]; ++j) chunks[j].g0 = g0;
-    }
   ChunkLists L;
   rc = lease_chunks(chunks, s, &L);
   if (rc) return rc;

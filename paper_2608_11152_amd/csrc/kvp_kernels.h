@@ -131,15 +131,16 @@ struct TierArgs {
   int maxp;
 };
 
-// Block hashing works on chunks of up to 64 full pages of one sequence.
+// Block hashing and prefix lookup work on chunks of up to 64 full pages of one sequence.
 struct HashChunk {
   int32_t t0;               // first token of the chunk
   int32_t o0;               // first output slot of the chunk
-  int32_t n;                // pages in the chunk (1..64)
+  int32_t n;                // pages in the chunk (1..64; 0: the only chunk of a sequence without a full page, lookup)
   int32_t c;                // chunk index within its sequence
-  int32_t g0;               // index of the sequence's first chunk
-  int32_t pad[3];           // the sequence's chunk count, the sequence, its full pages
+  int32_t n_chunks, seq, n_pages;  // of the sequence: its chunks, its index, its full pages
+  int32_t pad;
 };
+static_assert(sizeof(HashChunk) == 32, "read as two 16-byte pieces");
 
 struct HashArgs {
   const int32_t* tokens;
@@ -151,7 +152,7 @@ struct HashArgs {
 
 struct GroupLcpArgs {
   const uint64_t* hashes;
-  const int4* seq_info;     // as in HashArgs
+  const int4* seq_info;     // {first token, full pages, first hash slot, 0} per sequence (pinned host)
   const int32_t* grp_off;   // [num_groups + 1] offsets into members (pinned host)
   const int32_t* members;   // sequence ids of each group's members
   int32_t* shared_pages;    // [num_groups] device output
@@ -161,7 +162,7 @@ struct TableArgs {
   uint64_t* keys;           // [mask + 1]
   int32_t* vals;            // [mask + 1]
   uint64_t mask;
-  const uint64_t* hashes;   // insert / erase: [n]; lookup: per-page hashes laid out as seq_info says
+  const uint64_t* hashes;   // insert / erase: [n]; lookup: per-page hashes, sequence by sequence
   const int32_t* pages;     // insert / erase: [n]
   int64_t n;
   const HashChunk* chunks;  // lookup: 64-page chunks of the sequences (pinned host)

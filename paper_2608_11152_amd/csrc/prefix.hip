@@ -117,7 +117,7 @@ __global__ __launch_bounds__(kFinishChunks) void hash_finish_kernel(HashArgs a) 
   __shared__ uint64_t enter[LONG ? 1 : kFinishChunks];
   __shared__ uint64_t wave_a[kFinishWaves], wave_b[kFinishWaves];
   const HashChunk first = a.chunks[a.seq_first[blockIdx.x]];  // a sequence's first chunk
-  const int nch = first.pad[0], np = first.pad[2];
+  const int nch = first.n_chunks, np = first.n_pages;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   uint64_t* out = a.out + first.o0;
   const uint64_t g_lane = gamma_pow((unsigned)lane + 1), g_chunk = gamma_pow(64), g_63 = gamma_pow(63);
@@ -282,7 +282,7 @@ __global__ __launch_bounds__(64) void lookup_chunk_kernel(TableArgs a) {
 __global__ __launch_bounds__(64) void lookup_finish_kernel(TableArgs a) {
   const HashChunk ch = a.chunks[blockIdx.x];
   const int lane = threadIdx.x;
-  const int nch = ch.pad[0], np = ch.pad[2];
+  const int nch = ch.n_chunks, np = ch.n_pages;
   int32_t* out = a.out_pages + (ch.o0 - 64 * ch.c);  // the sequence's first page
   const int upto = ch.c == 0 ? nch : ch.c;
   int missing = -1;  // the earliest of chunks 0 .. upto - 1 with a miss
@@ -300,7 +300,7 @@ __global__ __launch_bounds__(64) void lookup_finish_kernel(TableArgs a) {
     const int p = 64 * missing + lane;
     matched = 64 * missing + (int)__builtin_ctzll(__ballot(p < np && out[p] < 0));
   }
-  if (lane == 0) a.matched[ch.pad[1]] = matched;
+  if (lane == 0) a.matched[ch.seq] = matched;
 }
 
 // Lookup pass 2 of calls with a long sequence: one workgroup per sequence finds the earliest miss and reports the
@@ -310,7 +310,7 @@ constexpr int kMissThreads = 1024;
 __global__ __launch_bounds__(kMissThreads) void lookup_miss_kernel(TableArgs a) {
   __shared__ int first;  // the earliest chunk with a miss
   const HashChunk ch = a.chunks[a.seq_first[blockIdx.x]];
-  const int nch = ch.pad[0], np = ch.pad[2];
+  const int nch = ch.n_chunks, np = ch.n_pages;
   const int32_t* out = a.out_pages + ch.o0;
   if (threadIdx.x == 0) first = INT32_MAX;
   __syncthreads();
@@ -333,13 +333,13 @@ __global__ __launch_bounds__(kMissThreads) void lookup_miss_kernel(TableArgs a) 
     const int64_t p = 64 * (int64_t)first + threadIdx.x;
     matched = 64 * first + (int)__builtin_ctzll(__ballot(p < np && out[p] < 0));
   }
-  if (threadIdx.x == 0) a.matched[ch.pad[1]] = matched;
+  if (threadIdx.x == 0) a.matched[ch.seq] = matched;
 }
 
 __global__ __launch_bounds__(64) void lookup_cut_kernel(TableArgs a) {
   const HashChunk ch = a.chunks[blockIdx.x];
   const int lane = threadIdx.x;
-  if (lane < ch.n && 64 * ch.c + lane >= a.matched[ch.pad[1]]) a.out_pages[ch.o0 + lane] = -1;
+  if (lane < ch.n && 64 * ch.c + lane >= a.matched[ch.seq]) a.out_pages[ch.o0 + lane] = -1;
 }
 
 __global__ void fill_table_kernel(uint64_t* keys, int32_t* vals, int64_t n) {
