@@ -318,23 +318,7 @@ struct DecodeLayout {
     auto put = [&](size_t off, const void* src, size_t n) {
       if (n) std::memcpy(dst + off, src, n);
     };
-    // Wave-path records: segment s's first chunk is record s, its further chunks follow all the first ones.
-    const int segs = (int)plan.seg_off.size() - 1;
-    auto* const recs = reinterpret_cast<kvp::DecodeRec*>(dst + off_wave);
-    const kvp::DecodeItem* it = plan.wave_items.data();
-    const int32_t *seg_off = plan.seg_off.data(), *members = plan.members.data(), *part_base = plan.part_base.data();
-    int32_t tail = segs;
-    for (int s = 0, c = 0; s < segs; ++s) {
-      const int c1 = seg_off[s + 1];
-      for (int32_t at = s; c < c1; ++c, ++it) {
-        const int32_t next = c + 1 < c1 ? tail++ : -1;
-        const int32_t seq = members[it->mem_off];
-        recs[at] = {it->row, it->page_lo, it->page_hi, it->tok_end,
-                    (uint32_t)it->kind | (uint32_t)(it->n_mem - 1) << 1 | (uint32_t)it->mem_off << 5, next,
-                    seq, it->slot < 0 ? -1 : part_base[seq] + it->slot};
-        at = next;
-      }
-    }
+    kvp::write_decode_recs(plan, reinterpret_cast<kvp::DecodeRec*>(dst + off_wave));
     put(off_group, plan.group_items.data(), plan.group_items.size() * sizeof(kvp::DecodeItem));
     put(off_members, plan.members.data(), plan.members.size() * 4);
     put(off_part_base, plan.part_base.data(), plan.part_base.size() * 4);

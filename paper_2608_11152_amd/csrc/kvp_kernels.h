@@ -44,20 +44,6 @@ struct GatherArgs {
   float scale_k, scale_v;
 };
 
-// A wave-path chunk as the kernel reads it, over the bus from pinned host memory: what a wave needs before its first
-// page in one record, so that a chunk of one member starts after one such read.  The segment's chunk range, the item
-// and its member list were three dependent reads of 1.3 us each (and the partial index a fourth, at the chunk's
-// end): one sequence of 131,007 tokens 58.1 -> 54.5 us, RLHF 178.0 -> 174.9 us, mixed 369.8 -> 363.6 us, RLVR 1392.8
-// -> 1376.5 us.  The other members of a chunk stay in the call's member list: records that hold them all (160 bytes
-// for 16) leave RLHF at 175.2 us and cost the host 3 us per 1000 short sequences.
-struct DecodeRec {
-  int32_t row, page_lo, page_hi, tok_end;  // as in DecodeItem
-  uint32_t kind_mem;          // kind, n_mem - 1 and mem_off in 1, 4 and 27 bits
-  int32_t next;               // record of the segment's next chunk, -1 = none
-  int32_t seq, part;          // the first member and the index of its partial, -1 = write the output
-};
-static_assert(sizeof(DecodeRec) == 32, "two 16-byte reads");
-
 struct DecodeArgs {
   const uint16_t* q;        // [B, Hq, D] bf16
   const uint16_t* layer;

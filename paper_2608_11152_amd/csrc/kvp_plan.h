@@ -36,6 +36,22 @@ struct DecodeItem {
 };
 static_assert(sizeof(DecodeItem) == 32, "DecodeItem is uploaded as raw bytes");
 
+// A wave-path chunk as the kernel reads it, over the bus from pinned host memory: what a wave needs before its first
+// page in one record, so that a chunk of one member starts after one such read.  The segment's chunk range, the item
+// and its member list were three dependent reads of 1.3 us each (and the partial index a fourth, at the chunk's
+// end): one sequence of 131,007 tokens 58.1 -> 54.5 us, RLHF 178.0 -> 174.9 us, mixed 369.8 -> 363.6 us, RLVR 1392.8
+// -> 1376.5 us.  The other members of a chunk stay in the call's member list: records that hold them all (160 bytes
+// for 16) leave RLHF at 175.2 us and cost the host 3 us per 1000 short sequences.
+struct DecodeRec {
+  int32_t row, page_lo, page_hi, tok_end;  // as in DecodeItem
+  uint32_t kind_mem;          // kind, n_mem - 1 and mem_off (0 for one member) in 1, 4 and 27 bits
+  int32_t next;               // record of the segment's next chunk, -1 = none
+  int32_t seq, part;          // the first member and the index of its partial, -1 = write the output
+};
+static_assert(sizeof(DecodeRec) == 32, "two 16-byte reads");
+
+constexpr int64_t kMaxSharedMembers = int64_t(1) << 27;  // offsets that kind_mem holds
+
 struct DecodePlan {
   std::vector<DecodeItem> wave_items;   // chunks in segment order (private and <= 16-column prefix)
   std::vector<int32_t> seg_off;         // [segments + 1]: chunks of segment s are seg_off[s]..seg_off[s+1]
@@ -60,9 +76,7 @@ struct PrefillItem {
   int32_t st_lo;     // first 64-key stage of the range (st_lo * 64 <= the session's cached length)
   int32_t st_hi;     // one past the last stage of the range
   int32_t slot;      // partial index of the range within each query row's list, -1 = write the output
-  int32_t pad[2];
 };
-static_assert(sizeof(PrefillItem) == 32, "PrefillItem is uploaded as raw bytes");
 
 // An item as the kernels read it: the planner's item with what they would otherwise look up.
 struct PrefillWork {
@@ -97,7 +111,11 @@ Status validate_group_prefix(const int32_t* lens, int B, const kvp_group_prefix*
 // chunk_start_pages: the start cost a segment's budget charges per chunk (kChunkStartPages for bf16
 // pools, kChunkStartPagesFp8 for FP8 pools).
 Status plan_decode(const int32_t* seq_lens, int B, int maxp, const kvp_group_prefix* gp, int Hq, int Hkv,
-                   DecodePlan* plan, int chunk_start_pages = kChunkStartPages);
+                   DecodePlan* plan, int chunk_start_pages = kChunkStartPages,
+                   int64_t max_shared_members = kMaxSharedMembers);
+// The wave path's records, one per chunk: segment s's first chunk is record s, its further chunks follow all the
+// first ones.
+void write_decode_recs(const DecodePlan& plan, DecodeRec* recs);
 Status plan_prefill(const int32_t* ctx_lens, const int32_t* cu_q, int B, int maxp, int Hq, int Hkv,
                     PrefillPlan* plan);
 // A plan's items as the kernels read them (ctx_lens, cu_q and G = Hq / Hkv as given to plan_prefill).

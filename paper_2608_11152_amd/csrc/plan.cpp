@@ -45,7 +45,7 @@ Status validate_group_prefix(const int32_t* lens, int B, const kvp_group_prefix*
 }
 
 Status plan_decode(const int32_t* seq_lens, int B, int maxp, const kvp_group_prefix* gp, int Hq, int Hkv,
-                   DecodePlan* plan, int chunk_start_pages) {
+                   DecodePlan* plan, int chunk_start_pages, int64_t max_shared_members) {
   *plan = DecodePlan();
   if (B < 0) return fail(KVP_EINVAL, "num_seqs %ld < 0", B);
   if (B > 0 && !seq_lens) return fail(KVP_EINVAL, "seq_lens is NULL");
@@ -130,6 +130,8 @@ Status plan_decode(const int32_t* seq_lens, int B, int maxp, const kvp_group_pre
       (wide ? group_units : wave_units).push_back(u);
     }
   }
+  if ((int64_t)plan->members.size() > max_shared_members)
+    return fail(KVP_EINVAL, "more than %ld members of shared prefixes", (long)max_shared_members);
   for (int i = 0; i < B; ++i) {
     if (seq_lens[i] <= 0) continue;
     const int lo = shared_of(i);
@@ -414,7 +416,7 @@ Status plan_prefill(const int32_t* ctx_lens, const int32_t* cu_q, int B, int max
     range_of(un.seq, un.k, t, &lo, &hi);
     load[x] += hi - lo;
     bins[x].push_back(PrefillItem{un.seq, un.kvh, t * kPrefillRows, lo, hi,
-                                  plan->nsplit[un.seq] == 1 ? -1 : un.k, {0, 0}});
+                                  plan->nsplit[un.seq] == 1 ? -1 : un.k});
   };
   // the least-loaded XCD with room for n more workgroups, or -1
   auto pick = [&](size_t n) {
@@ -437,11 +439,29 @@ Status plan_prefill(const int32_t* ctx_lens, const int32_t* cu_q, int B, int max
   }
   size_t longest = 0;
   for (auto& b : bins) longest = std::max(longest, b.size());
-  plan->items.assign(longest * kXcd, PrefillItem{-1, 0, 0, 0, 0, -1, {0, 0}});
+  plan->items.assign(longest * kXcd, PrefillItem{-1, 0, 0, 0, 0, -1});
   for (int x = 0; x < kXcd; ++x)
     for (size_t j = 0; j < bins[x].size(); ++j) plan->items[j * kXcd + x] = bins[x][j];
   plan->real_items = tiles_total;
   return {};
+}
+
+void write_decode_recs(const DecodePlan& plan, DecodeRec* recs) {
+  const int segs = (int)plan.seg_off.size() - 1;
+  const DecodeItem* it = plan.wave_items.data();
+  int32_t tail = segs;
+  for (int s = 0, c = 0; s < segs; ++s) {
+    const int c1 = plan.seg_off[s + 1];
+    for (int32_t at = s; c < c1; ++c, ++it) {
+      const int32_t next = c + 1 < c1 ? tail++ : -1;
+      const int32_t seq = plan.members[it->mem_off];
+      const uint32_t mem_off = it->n_mem > 1 ? (uint32_t)it->mem_off : 0u;
+      recs[at] = {it->row, it->page_lo, it->page_hi, it->tok_end,
+                  (uint32_t)it->kind | (uint32_t)(it->n_mem - 1) << 1 | mem_off << 5, next,
+                  seq, it->slot < 0 ? -1 : plan.part_base[seq] + it->slot};
+      at = next;
+    }
+  }
 }
 
 std::vector<PrefillWork> prefill_work(const PrefillPlan& plan, const int32_t* ctx_lens, const int32_t* cu_q, int G) {

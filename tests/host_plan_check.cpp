@@ -10,6 +10,7 @@
 //            of a tile tile [0, its last key] without gaps or overlaps;
 //            a split call, and any call of at most one round, keeps every XCD within its share of the
 //            resident workgroups;
+//   the records and work items made of plans hold what the kernels would otherwise look up;
 //   both:    plans are deterministic, and invalid inputs return the documented error codes.
 // `self-test` plants mistakes into plans and expects the checks to reject each of them.
 #include <algorithm>
@@ -119,6 +120,65 @@ static bool check_decode(const DecodeCase& c, const DecodePlan& P, int K = kvp::
   return true;
 }
 
+// The records the wave path reads: segment s starts at record s, follows its chunks in order and ends; every record is
+// reached once.
+static bool check_recs(const DecodePlan& P, const std::vector<kvp::DecodeRec>& R) {
+  std::vector<int> used(R.size(), 0);
+  for (size_t s = 0; s + 1 < P.seg_off.size(); ++s) {
+    int r = (int)s;
+    for (int c = P.seg_off[s]; c < P.seg_off[s + 1]; ++c) {
+      EXPECT(r >= 0 && r < (int)R.size() && !used[r]++, "record %d", r);
+      const DecodeItem& it = P.wave_items[c];
+      const kvp::DecodeRec& x = R[r];
+      EXPECT(x.row == it.row && x.page_lo == it.page_lo && x.page_hi == it.page_hi && x.tok_end == it.tok_end,
+             "record %d: range", r);
+      EXPECT((int)(x.kind_mem & 1) == it.kind && (int)((x.kind_mem >> 1) & 15) + 1 == it.n_mem, "record %d: kind", r);
+      EXPECT(x.seq == P.members[it.mem_off], "record %d: first member", r);
+      EXPECT(x.part == (it.slot < 0 ? -1 : P.part_base[x.seq] + it.slot), "record %d: partial", r);
+      for (int m = 1; m < it.n_mem; ++m)
+        EXPECT((int)(x.kind_mem >> 5) + m == it.mem_off + m, "record %d: member list", r);
+      r = x.next;
+    }
+    EXPECT(r == -1, "segment %zu does not end", s);
+  }
+  EXPECT(std::count(used.begin(), used.end(), 1) == (int)R.size(), "records that no segment reaches");
+  return true;
+}
+
+// The segment budget is the smallest at which cutting the units chunk by chunk fits the target.
+static bool check_budget(const DecodePlan& P, int Hkv, int K) {
+  std::vector<int> units;  // pages
+  int64_t total = 0;
+  for (size_t c = 0; c < P.wave_items.size(); ++c) {
+    const DecodeItem &it = P.wave_items[c], *prev = c ? &P.wave_items[c - 1] : nullptr;
+    const int n = it.page_hi - it.page_lo;
+    if (prev && prev->row == it.row && prev->kind == it.kind && prev->mem_off == it.mem_off) units.back() += n;
+    else units.push_back(n);
+    total += n;
+  }
+  const int64_t target =
+      std::max<int64_t>(1, (std::max<int64_t>(1, kvp::kDecodeWaves / 4) - P.group_reserved_blocks) * 4 / Hkv);
+  const int64_t least = std::max<int64_t>(kvp::kMinSegmentPages, ((total + target - 1) / target + 1) & ~int64_t(1)) + K;
+  auto segments = [&](int64_t cap) {
+    int64_t fill = 0, seg = 0;
+    for (int left : units)
+      while (left > 0) {
+        if (fill > 0 && fill + K >= cap) fill = 0, ++seg;
+        fill += K;
+        const int64_t take = std::min<int64_t>(left, cap - fill);
+        left -= (int)take;
+        fill += take;
+        if (fill >= cap) fill = 0, ++seg;
+      }
+    return seg + (fill > 0);
+  };
+  const int64_t cap = P.pages_per_split + K;
+  EXPECT(segments(cap) == (int64_t)P.seg_off.size() - 1 && segments(cap) <= target, "%lld segments, %zu planned",
+         (long long)segments(cap), P.seg_off.size() - 1);
+  EXPECT(cap >= least && (cap == least || segments(cap - 1) > target), "budget %lld is not the smallest", (long long)cap);
+  return true;
+}
+
 struct PrefillCase {
   std::vector<int32_t> ctx, cuq;
   int Hq = 32, Hkv = 4, maxp = 0;
@@ -196,6 +256,29 @@ static bool check_prefill(const PrefillCase& c, const PrefillPlan& P) {
   return true;
 }
 
+static bool check_work(const PrefillCase& c, const PrefillPlan& P, const std::vector<kvp::PrefillWork>& W) {
+  const int G = c.Hq / c.Hkv;
+  EXPECT(W.size() == P.items.size(), "work items");
+  int64_t stages = 0, real = 0;
+  for (size_t k = 0; k < W.size(); ++k) {
+    const PrefillItem& it = P.items[k];
+    const kvp::PrefillWork& w = W[k];
+    EXPECT((w.seq < 0) == (it.seq < 0), "work item %zu", k);
+    if (it.seq < 0) continue;
+    const int i = it.seq, nrows = (c.cuq[i + 1] - c.cuq[i]) * G;
+    EXPECT(w.seq == i && w.kvh == it.kvh && w.row0 == it.row0 && w.st_lo == it.st_lo && w.slot == it.slot, "work item %zu", k);
+    EXPECT(w.nst == it.st_hi - it.st_lo && w.nst >= 1, "work item %zu: %d stages", k, w.nst);
+    EXPECT(w.ctx == c.ctx[i] && w.q0 == c.cuq[i] && w.nrows == nrows, "work item %zu: session", k);
+    const int last = std::min(nrows, it.row0 + kvp::kPrefillRows) - 1;
+    EXPECT(w.n_keys == c.ctx[i] + last / G + 1, "work item %zu: %d keys", k, w.n_keys);
+    EXPECT(w.part0 == P.part_base[i] && w.nsplit == P.nsplit[i], "work item %zu: partials", k);
+    stages += w.nst;
+    ++real;
+  }
+  EXPECT(kvp::prefill_mean_stages(P) == (real ? stages / real : 0), "mean stages");
+  return true;
+}
+
 static std::mt19937_64 rng;
 static int uni(int lo, int hi) { return std::uniform_int_distribution<int>(lo, hi)(rng); }
 
@@ -257,6 +340,12 @@ static bool same_plan(const DecodePlan& a, const DecodePlan& b) {
          eq(a.seg_off, b.seg_off) && eq(a.part_base, b.part_base) && a.total_parts == b.total_parts;
 }
 
+static std::vector<kvp::DecodeRec> recs_of(const DecodePlan& P) {
+  std::vector<kvp::DecodeRec> R(P.wave_items.size());
+  kvp::write_decode_recs(P, R.data());
+  return R;
+}
+
 static bool run_decode(const DecodeCase& c) {
   kvp_group_prefix gp = gp_of(c);
   DecodePlan P, Q;
@@ -264,12 +353,13 @@ static bool run_decode(const DecodeCase& c) {
   EXPECT(s.ok(), "plan_decode failed: %s", s.msg.c_str());
   kvp::plan_decode(c.lens.data(), (int)c.lens.size(), c.maxp, &gp, c.Hq, c.Hkv, &Q);
   EXPECT(same_plan(P, Q), "plan_decode is not deterministic");
-  if (!check_decode(c, P)) return false;
+  if (!check_decode(c, P) || !check_budget(P, c.Hkv, kvp::kChunkStartPages) || !check_recs(P, recs_of(P))) return false;
   // the FP8-pool plan: the same properties under its larger chunk-start cost
   DecodePlan F;
   s = kvp::plan_decode(c.lens.data(), (int)c.lens.size(), c.maxp, &gp, c.Hq, c.Hkv, &F, kvp::kChunkStartPagesFp8);
   EXPECT(s.ok(), "plan_decode (FP8 cost) failed: %s", s.msg.c_str());
-  return check_decode(c, F, kvp::kChunkStartPagesFp8);
+  return check_decode(c, F, kvp::kChunkStartPagesFp8) && check_budget(F, c.Hkv, kvp::kChunkStartPagesFp8) &&
+         check_recs(F, recs_of(F));
 }
 
 static int g_split_sessions = 0;
@@ -283,7 +373,7 @@ static bool run_prefill(const PrefillCase& c) {
   EXPECT(P.items.size() == Q.items.size() &&
              (P.items.empty() || !std::memcmp(P.items.data(), Q.items.data(), P.items.size() * sizeof(PrefillItem))),
          "plan_prefill is not deterministic");
-  return check_prefill(c, P);
+  return check_prefill(c, P) && check_work(c, P, kvp::prefill_work(P, c.ctx.data(), c.cuq.data(), c.Hq / c.Hkv));
 }
 
 // The prefill kernel a call gets: where the kernel for long key ranges was measured slower than the other, it must
@@ -340,6 +430,10 @@ static bool run_errors() {
   d = c;
   d.shared[0] = -1;
   EXPECT(code(d, 32, 4) == KVP_EGROUP, "negative shared pages");
+  EXPECT(kvp::plan_decode(c.lens.data(), 2, c.maxp, &gp, 32, 4, &P, kvp::kChunkStartPages, 2).code == KVP_OK,
+         "as many shared members as a record's offset holds");
+  EXPECT(kvp::plan_decode(c.lens.data(), 2, c.maxp, &gp, 32, 4, &P, kvp::kChunkStartPages, 1).code == KVP_EINVAL,
+         "more shared members than a record's offset holds");
   EXPECT(kvp::plan_decode(c.lens.data(), -1, c.maxp, &gp, 32, 4, &P).code == KVP_EINVAL, "negative count");
   // tables: valid, an id outside the pool, a member whose shared entries differ
   std::vector<int32_t> bt = {0, 1, 2, -1, 0, 1, 3, 4};
@@ -391,6 +485,22 @@ static bool self_test() {
     b.total_parts += 1;
     expect_reject(b);
   }
+  if (!P.wave_items.empty()) {
+    auto expect_recs_reject = [&](auto&& change) {
+      std::vector<kvp::DecodeRec> r = recs_of(P);
+      change(r);
+      ++planted;
+      if (!check_recs(P, r)) ++rejected;
+    };
+    expect_recs_reject([](auto& r) { r[0].part += 1; });       // another sequence's partial
+    expect_recs_reject([](auto& r) { r[0].next = 0; });        // a segment that does not end
+    expect_recs_reject([](auto& r) { r.back().seq += 1; });    // another member
+    expect_recs_reject([](auto& r) { r[0].kind_mem ^= 2; });   // another member count
+    DecodePlan b = P;
+    b.pages_per_split += 1;  // a budget that is not the smallest
+    ++planted;
+    if (!check_budget(b, c.Hkv, kvp::kChunkStartPages)) ++rejected;
+  }
   PrefillCase pc;
   pc.ctx = {5000};
   pc.cuq = {0, 300};
@@ -411,6 +521,13 @@ static bool self_test() {
       break;
     }
   {
+    std::vector<kvp::PrefillWork> w = kvp::prefill_work(Q, pc.ctx.data(), pc.cuq.data(), pc.Hq / pc.Hkv);
+    for (auto& x : w)
+      if (x.seq >= 0) x.n_keys += 1;  // a key no row sees
+    ++planted;
+    if (!check_work(pc, Q, w)) ++rejected;
+  }
+  {
     // one XCD given a workgroup past its share of the round
     PrefillPlan b = Q;
     size_t last = 0;
@@ -418,7 +535,7 @@ static bool self_test() {
       if (b.items[j].seq >= 0) last = j;
     const PrefillItem moved = b.items[last];
     b.items[last].seq = -1;
-    b.items.resize((size_t)kvp::kPrefillSplitTarget + 8, PrefillItem{-1, 0, 0, 0, 0, -1, {0, 0}});
+    b.items.resize((size_t)kvp::kPrefillSplitTarget + 8, PrefillItem{-1, 0, 0, 0, 0, -1});
     b.items[(size_t)kvp::kPrefillSplitTarget + last % 8] = moved;
     ++planted;
     if (!check_prefill(pc, b)) ++rejected;
