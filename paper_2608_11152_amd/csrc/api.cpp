@@ -1,6 +1,6 @@
-// C-ABI of libkvpattn: pool management, kv_append / kv_gather, paged_decode_attn and
-// prefix_chunk_prefill_attn.  Host metadata is validated and planned here, packed into one buffer and
-// uploaded with a single asynchronous copy from a ring of pinned staging slots; then the kernels are
+// C-ABI of libkvpattn: pool management, kv_append / kv_gather, the attention calls, the host tier, block hashing and
+// the prefix table.  Host metadata is validated and planned here and packed into a piece of a pinned block
+// (staging.h), where the kernels read it, or which a copy kernel brings into the caller's workspace; the kernels are
 // launched on the caller's stream.  Nothing in this file computes attention.
 #include <hip/hip_runtime.h>
 
@@ -193,7 +193,7 @@ void build_runs(const int32_t* start, const int64_t* first_src, const int32_t* c
   }
 }
 
-// Per-sequence {first token, full pages, first hash slot, 0} from host cu_tokens, in a leased pinned slot
+// Per-sequence {first token, full pages, first hash slot, 0} from host cu_tokens, in a leased pinned piece
 // (appended after `extra` bytes the caller packs first).  Returns the total full-page count in *pages.
 int lease_seq_info(const int32_t* cu_tokens, int num_seqs, hipStream_t s, Staging::Lease* lease, int64_t* pages,
                    const std::vector<unsigned char>& extra, size_t* info_off) {
@@ -271,7 +271,7 @@ int lease_chunks(const std::vector<kvp::HashChunk>& chunks, hipStream_t s, Chunk
 }
 
 // Page moves between the pool and the host tier: the item list is read by the kernel straight from a
-// pinned staging slot, released after the kernel.
+// pinned piece, released after the kernel.
 int run_tier(kvp_pool_t pool, int layer, const std::vector<kvp::TierItem>& items, void* host, int32_t* bt,
              int maxp, bool restore, hipStream_t s) {
   Staging::Lease lease;
@@ -293,7 +293,7 @@ int run_tier(kvp_pool_t pool, int layer, const std::vector<kvp::TierItem>& items
   return rr;
 }
 
-// Page runs of kv_append / kv_gather in a leased pinned slot: each wave reads its one 24-byte record
+// Page runs of kv_append / kv_gather in a leased pinned piece: each wave reads its one 24-byte record
 // there, so no device buffer, copy or allocation sits in the stream ahead of the kernel.
 int lease_runs(const std::vector<kvp::PageRun>& runs, hipStream_t s, Staging::Lease* lease) {
   const size_t n = runs.size() * sizeof(kvp::PageRun);
@@ -303,7 +303,7 @@ int lease_runs(const std::vector<kvp::PageRun>& runs, hipStream_t s, Staging::Le
   return KVP_OK;
 }
 
-// Decode: the work list lives in a pinned staging slot (read by the kernels directly); the caller's
+// Decode: the work list lives in a pinned staging piece (read by the kernels directly); the caller's
 // workspace holds [partial accumulators][partial (m, l)].
 struct DecodeLayout {
   kvp::DecodePlan plan;
@@ -881,7 +881,7 @@ int kvp_group_shared_pages(const uint64_t* hashes, const int32_t* cu_tokens, int
   std::vector<int32_t> members(std::max(1, cnt[num_groups])), fill(cnt.begin(), cnt.end() - 1);
   for (int i = 0; i < num_seqs; ++i)
     if (group_id[i] >= 0) members[fill[group_id[i]]++] = i;
-  // pinned slot: [grp_off | members | seq_info]
+  // pinned piece: [grp_off | members | seq_info]
   std::vector<unsigned char> extra;
   const size_t moff = ((cnt.size() * 4) + 255) & ~size_t(255);
   extra.resize(moff + members.size() * 4);
@@ -1058,9 +1058,9 @@ int paged_decode_attn(const void* q, kvp_pool_t pool, int layer, const int32_t* 
   if (L.total > 0 && (!ws || ws_bytes < L.total))
     return set_err(KVP_EWORKSPACE, "workspace of %zu bytes, %zu needed", ws ? ws_bytes : (size_t)0, L.total);
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-  // The work list is read by the kernels straight from a pinned staging slot (a few KB to a few
+  // The work list is read by the kernels straight from a pinned staging piece (a few KB to a few
   // hundred KB, read once per wave), so no copy sits between the caller's previous work and the
-  // decode kernels.  The slot is released after the last kernel that reads it.
+  // decode kernels.  The piece is released after the last kernel that reads it.
   Staging::Lease lease;
   rc = staging().lease(L.meta_bytes, s, &lease);
   if (rc) return rc;
@@ -1178,7 +1178,7 @@ int mixed_step_attn(kvp_pool_t pool, int layer, int num_q_heads, float scale, in
   Staging::Lease lease, lease_pf;
   const unsigned char* meta_pf = nullptr;
   if (num_dec > 0) {
-    // the decode work list is read from a pinned staging slot, as in paged_decode_attn
+    // the decode work list is read from a pinned staging piece, as in paged_decode_attn
     rc = staging().lease(L.dec.meta_bytes, s, &lease);
     if (rc) return rc;
     L.dec.write_meta(reinterpret_cast<unsigned char*>(lease.host));

@@ -1,4 +1,4 @@
-"""mixed_step_attn: the decode and chunk-prefill work of one step in one launch.  Its outputs must equal,
+"""mixed_step_attn: the decode and chunk-prefill work of one step in one call.  Its outputs must equal,
 bit for bit, paged_decode_attn followed by prefix_chunk_prefill_attn with the same arguments (the same
 plans and the same block bodies), and stay within tolerance of the oracle; either part may be empty, and
 a host-detected error leaves the outputs untouched."""
@@ -35,9 +35,9 @@ def _run_both_ways(pool, w, q, qp, bt, gp):
 
 @pytest.mark.parametrize("name,over", [("mixed_s", {}), ("agentic_s", {}), ("mixed_s", dict(Hq=8, Hkv=2, d=64))])
 def test_mixed_step_equals_the_two_calls(name, over):
-    """mixed_s: split-KV decode partials and prefill history splits (fewer than 512 tiles) in the fused
-    launch, wide groups on the LDS-staged prefix blocks in their own launch ahead of it; agentic_s: no
-    groups; d = 64 with GQA 8/2."""
+    """mixed_s: split-KV decode partials and prefill history splits (fewer than kPrefillSplitTarget = 256
+    tiles), wide groups on the LDS-staged prefix blocks in their own launch ahead of the shared one;
+    agentic_s: no groups; d = 64 with GQA 8/2."""
     import torch
     note(f"mixed_step {name} {over}")
     w = W.make_workload(name, **over)
