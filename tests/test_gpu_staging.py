@@ -59,3 +59,41 @@ def test_metadata_blocks_under_pending_work(n_streams, calls, behind):
         assert torch.equal(kk, want) and torch.equal(vv, want)
         pool.close()
     scratch.close()
+
+
+@pytest.mark.parametrize("stream", [None, 2], ids=["one stream", "hipStreamPerThread"])
+def test_threads(stream):
+    """Four threads append at once, to pools of their own: on the null stream they share blocks; hipStreamPerThread
+    (the handle 2) names another stream in each."""
+    import threading
+    import torch
+    T, calls, B, Hkv, d = 4, 40, 4000, 1, 64
+    maxp = (calls + 15) // 16
+    pools = [kp.Pool(1, B * maxp, Hkv, d) for _ in range(T)]
+    bt = torch.randperm(B * maxp, device="cuda").to(torch.int32).view(B, maxp).contiguous()
+    x = torch.randn(T, calls, B, Hkv, d, device="cuda").to(torch.bfloat16)
+    cu = np.arange(B + 1, dtype=np.int32)
+    torch.cuda.synchronize()
+    note(f"metadata blocks: {T} threads, stream {stream}")
+    failed = []
+
+    def work(t):
+        try:
+            for c in range(calls):
+                kp.kv_append(pools[t], 0, x[t, c], x[t, c], bt, np.full(B, c, np.int32), cu, stream=stream)
+        except Exception as e:  # reported by the test, below
+            failed.append(e)
+
+    threads = [threading.Thread(target=work, args=(t,)) for t in range(T)]
+    for th in threads:
+        th.start()
+    for th in threads:
+        th.join()
+    torch.cuda.synchronize()
+    assert not failed, failed
+    for t, pool in enumerate(pools):
+        kk, vv = kp.kv_gather(pool, 0, bt, np.full(B, calls, np.int32))
+        assert pool.device_error() == kp.KVP_OK
+        want = x[t].transpose(0, 1).reshape(B * calls, Hkv, d)
+        assert torch.equal(kk, want) and torch.equal(vv, want)
+        pool.close()
