@@ -96,8 +96,8 @@ class StagingOf {
     for (const Block& x : blocks_) open += x.state == kOpen && !x.closing;
     if (!b.closing && open <= kMaxOpen) return KVP_OK;
     const int rc = close(&b);
-    if (rc == KVP_OK || launched) return rc;
-    b.state = kFree;  // a stream that takes neither the launch nor an event has no work
+    if (rc == KVP_OK || launched || b.stream == Stream{}) return rc;
+    b.state = kFree;  // a call's own block: a stream that takes neither the launch nor an event has no work
     return KVP_OK;    // (the caller reports the launch)
   }
 

@@ -230,6 +230,26 @@ void failed_launches() {
   w.drain();
 }
 
+// A failed launch does not give back a block of the null stream whose event cannot be recorded: calls before it may
+// still be reading their pieces.
+void failed_launch_in_a_shared_block() {
+  World w;
+  w.s.stream(5);
+  CHECK(w.call(0, 100 << 10) == KVP_OK);
+  Staging::Lease a, b;
+  CHECK(w.st.lease(100, 0, &a) == KVP_OK);
+  CHECK(w.st.lease(1 << 20, 0, &b) == KVP_OK);  // no room: the block closes with the call that holds a
+  w.s.bad_stream = 0;
+  (void)w.st.release(a, false);
+  w.s.bad_stream = -1;
+  for (int c = 0; c < 50; ++c) {
+    CHECK(w.call(5, 100 << 10) == KVP_OK);
+    while (w.s.step(*w.s.handles[5])) {}
+  }
+  CHECK(w.st.release(b, true) == KVP_OK);
+  w.drain();
+}
+
 // Eight calls at once on other streams beside the null stream's block of each of four devices; the thirteenth
 // block is refused.
 void concurrent_calls() {
@@ -259,6 +279,7 @@ int main(int argc, char** argv) {
   events_per_block();
   capture_refused();
   failed_launches();
+  failed_launch_in_a_shared_block();
   concurrent_calls();
   for (unsigned k = 0; k < 40; ++k) random_calls(seed * 1000 + k, 300);
   std::printf("ok: staging blocks\n");
